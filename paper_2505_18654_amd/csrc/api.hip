@@ -191,14 +191,10 @@ mtgr::AttnArgs make_args(const mtgr_hstu_problem_t* p, const AttnLayout& L, cons
 mtgr_status_t schedule(const mtgr_hstu_problem_t* p, const AttnLayout& L, const int32_t* offsets,
                        const int8_t* seg, const int32_t* ts, void* workspace, hipStream_t s) {
     char* ws = (char*)workspace;
-    hipError_t e = mtgr::launch_tile_summaries(offsets, seg, ts, p->num_users, L.ntile,
-                                               (int4*)(ws + L.off_summ), (int*)(ws + L.off_code), s);
-    if (e != hipSuccess) return device_fail(e, "tile summaries");
-    e = mtgr::launch_build_schedule(offsets, p->num_users, p->num_heads, L.tile,
-                                    (int2*)(ws + L.off_items), (int)L.slots, (int*)(ws + L.off_sorted), s);
-    if (e != hipSuccess) return device_fail(e, "schedule");
-    e = mtgr::launch_ds_offsets(offsets, p->num_users, p->num_heads, (long long*)(ws + L.off_dsoff), s);
-    if (e != hipSuccess) return device_fail(e, "dS offsets");
+    hipError_t e = mtgr::launch_plan(offsets, seg, ts, p->num_users, L.ntile, (int4*)(ws + L.off_summ),
+                                     (int*)(ws + L.off_code), p->num_heads, L.tile, (int2*)(ws + L.off_items),
+                                     (int)L.slots, (int*)(ws + L.off_sorted), (long long*)(ws + L.off_dsoff), s);
+    if (e != hipSuccess) return device_fail(e, "plan");
     return MTGR_SUCCESS;
 }
 

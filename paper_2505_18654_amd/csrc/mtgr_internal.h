@@ -49,10 +49,10 @@ struct AttnArgs {
 long long schedule_slots(long long total_tokens, int num_users, int max_seqlen, int heads, int bm);
 
 // Launchers; each returns the hipError_t of its launch.
-hipError_t launch_tile_summaries(const int* offsets, const int8_t* seg, const int* ts, int num_users,
-                                 int ntile, int4* summ, int* tok_code, hipStream_t s);
-hipError_t launch_build_schedule(const int* offsets, int num_users, int heads, int bm, int2* items,
-                                 int slots, int* sorted_users, hipStream_t s);
+// The batch plan: tile summaries, token codes, work list and stored-dS offsets.
+hipError_t launch_plan(const int* offsets, const int8_t* seg, const int* ts, int num_users, int ntile, int4* summ,
+                       int* tok_code, int heads, int bm, int2* items, int slots, int* sorted_users,
+                       long long* ds_off, hipStream_t s);
 hipError_t launch_fill_f32(float* p, long long n, float value, hipStream_t s);
 
 hipError_t launch_attn_fwd_bf16(const AttnArgs& a, int head_dim, int slots, hipStream_t s);
@@ -70,8 +70,6 @@ constexpr size_t DS_BLOCK_BYTES = 64 * 64 * 2;   // one stored-dS block (64 keys
 
 hipError_t launch_attn_bwd_bf16(const AttnArgs& a, int head_dim, int slots, const BwdPlan& plan,
                                 hipStream_t s);
-hipError_t launch_ds_offsets(const int* offsets, int num_users, int heads, long long* ds_off,
-                             hipStream_t s);
 // Vector-ALU backward: fp32 storage at any supported head_dim, or bf16 storage at head_dim 16.
 hipError_t launch_attn_bwd_vec(const AttnArgs& a, bool bf16, int head_dim, int slots, bool dq, bool dkdv,
                                hipStream_t s);
