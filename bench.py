@@ -70,6 +70,7 @@ KERNEL_SOURCES = {
     "gln_fwd_kernel": ["group_ln.hip"],
     "gln_bwd_kernel": ["group_ln.hip"],
     "gemm_bf16_kernel": ["gemm.hip"],
+    "gemm_wide_kernel": ["gemm_wide.hip"],
 }
 SHARED_SOURCES = ["mtgr_device.h", "mtgr_internal.h"]
 

@@ -21,7 +21,7 @@ LIB_NAME = "libmtgr_hstu.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
 SOURCES = ["api.hip", "schedule.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_bwd_dq.hip",
            "attn_bwd_dkdv.hip", "attn_bwd_dqds.hip", "group_ln.hip", "validate.hip",
-           "pointwise.hip", "embedding.hip", "gemm.hip", "clock.hip"]
+           "pointwise.hip", "embedding.hip", "gemm.hip", "gemm_wide.hip", "clock.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -45,7 +45,7 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build(jobs: int = 5) -> str:
+def build(jobs: int = 6) -> str:
     """Compile every HIP source for gfx950 and link the shared library."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:

@@ -690,9 +690,13 @@ mtgr_status_t check_gemm(int layout, int64_t M, int64_t N, int64_t K, int epilog
         return fail(MTGR_ERROR_UNSUPPORTED, "K = %lld is not a multiple of 32", (long long)K);
     if (layout == MTGR_GEMM_TN && M % 8 != 0)
         return fail(MTGR_ERROR_UNSUPPORTED, "M = %lld is not a multiple of 8 (MTGR_GEMM_TN)", (long long)M);
-    int mb, nb, s, per;
-    mtgr::gemm_plan(layout, M, N, K, &mb, &nb, &s, &per);
-    if ((long long)((mb + mtgr::XCDS - 1) / mtgr::XCDS) * mtgr::XCDS * nb * s >= (1ll << 24))
+    mtgr::GemmArgs g{};
+    g.layout = layout;
+    g.M = M;
+    g.N = N;
+    g.K = K;
+    mtgr::gemm_plan(&g);
+    if ((long long)((g.mblocks + mtgr::XCDS - 1) / mtgr::XCDS) * mtgr::XCDS * g.nblocks * g.splits >= (1ll << 24))
         return fail(MTGR_ERROR_UNSUPPORTED, "problem too large for one launch");
     return MTGR_SUCCESS;
 }
@@ -761,7 +765,7 @@ mtgr_status_t mtgr_gemm_bf16(int32_t layout, int64_t M, int64_t N, int64_t K, co
     g.ldr = ldr;
     g.bias = bias;
     g.colsum = colsum;
-    mtgr::gemm_plan(layout, M, N, K, &g.mblocks, &g.nblocks, &g.splits, &g.ks_per_split);
+    mtgr::gemm_plan(&g);
     if (layout == MTGR_GEMM_TN) {
         const size_t need = align256(mtgr::gemm_workspace_bytes(layout, M, N, K));
         if (workspace_bytes < need)

@@ -29,6 +29,8 @@
 // the supplier rows chosen so that both operands use the natural k order of the instruction
 // (lane half hf holds k = 8 hf .. 8 hf + 7).  Both layouts are swizzled so that every operand
 // read and every copy is free of bank conflicts.
+//
+// Large products run on the 256 x 256 tiles of gemm_wide.hip (gemm_plan decides).
 #include <type_traits>
 
 #include "mtgr_device.h"
@@ -87,24 +89,16 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmArgs g) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int col = lane & 31, hf = lane >> 5;
     const int wm = w & 1, wn = w >> 1;
-    // workgroups of one XCD (blockIdx % 8) take the n blocks of one m block one after another,
-    // so the A rows of that block stay in the XCD's L2; with fewer m blocks than XCDs (the weight
-    // gradients: M = d) each m block's n blocks are dealt to 8 / mblocks XCDs, so that no XCD
-    // is left without work
-    const int bid = blockIdx.x, x = bid % XCDS, jx = bid / XCDS;
-    int mb, nb;
-    if (g.mblocks >= XCDS) {
-        mb = x + XCDS * (jx / g.nblocks);
-        nb = jx % g.nblocks;
-    } else {
-        const int r = XCDS / g.mblocks;
-        mb = x / r;
-        nb = x % r + r * jx;
-        if (nb >= g.nblocks) return;
-    }
-    if (mb >= g.mblocks) return;
+    // Items (split, m block, n block), an equal share of consecutive ones per XCD (blockIdx % 8): the
+    // n blocks of an m block, and the m blocks of a K split, run on one XCD, so that their rows
+    // stay in its L2.  (Dealing m blocks to XCDs left two of them without work at three m blocks;
+    // weight gradients at K = 70,176, d = 256: 54 -> 36 us, at K = 16,000, d = 128: 22 -> 17 us; at
+    // K = 6,925, d = 512 it is the slower one, 21 -> 25 us.)
+    const int tiles = g.mblocks * g.nblocks, items = tiles * g.splits, share = (items + XCDS - 1) / XCDS;
+    const int item = blockIdx.x % XCDS * share + blockIdx.x / XCDS;
+    if (item >= items) return;
+    const int mb = item % tiles / g.nblocks, nb = item % g.nblocks, split = item / tiles;
     const int m0 = mb * GBM, n0 = nb * GBN;
-    const int split = blockIdx.y;
     const int nks = (int)((g.K + GBK - 1) / GBK);
     const int ks_begin = split * g.ks_per_split;
     const int nk = min(nks, ks_begin + g.ks_per_split) - ks_begin;     // >= 1 by the plan
@@ -495,52 +489,68 @@ __global__ __launch_bounds__(256) void gemm_split_reduce_kernel(GemmArgs g, int 
     }
 }
 
-void gemm_plan(int layout, long long M, long long N, long long K, int* mblocks, int* nblocks, int* splits,
-               int* ks_per_split) {
-    *mblocks = (int)((M + GBM - 1) / GBM);
-    *nblocks = (int)((N + GBN - 1) / GBN);
-    const int nks = (int)((K + GBK - 1) / GBK);
-    int s = 1;
-    if (*mblocks == 0 || *nblocks == 0 || nks == 0) {     // empty product: nothing is launched
-        *splits = 1;
-        *ks_per_split = 0;
-        return;
+// Which kernel: 256 x 128 tiles, two workgroups per CU (gemm_bf16_kernel), or 256 x 256 tiles, one
+// per CU (gemm_wide_kernel).  The wide one does the same work 1.1 (K below 2048) to 1.25 times
+// faster, but in whole rounds of 256 tiles, and a lone tile takes twice as long.  So NN / NT take it
+// when rounds of the narrow one, twice as short, would not beat it: M = 70,176, N = 512, K = 2048
+// (3 rounds of wide, 5 half rounds of narrow) 171 -> 157 us; M = 33,000, N = 512 (2 and 3) 88 -> 94 us
+// stays; M = 6,925, N = 1024, K = 4096 (1 and 1) 66 -> 86 us stays.  With bias + SiLU, whose
+// element work dominates at small K, the wide one is the faster at every size up to K = 768
+// (M = 700, d = 128: 17.3 -> 13.9 us; d = 768: 25.3 -> 27.5 us).  TN takes it when its splits fill
+// about half the chip (M = N = 768, K = 6,925, 117 workgroups: 42 -> 32 us; 512, 52 workgroups: 21 ->
+// 31 us stays).
+static bool use_wide(const GemmArgs& g, long long mb, long long nb, long long nb_narrow) {
+    auto rounds = [](long long tiles) { return (tiles + 255) / 256; };
+    if (mb * nb >= (1 << 20)) return false;
+    if (g.layout == GEMM_TN) {
+        const long long s = max(1ll, min(min(256 / max(mb * nb, 1ll), g.K / 512), 64ll));
+        return mb * nb * s >= 112;
     }
-    if (layout == GEMM_TN) {
-        // enough workgroups for two per CU, each split at least 8 k steps
-        const long long tiles = (long long)*mblocks * *nblocks;
-        s = (int)((512 + tiles - 1) / tiles);
-        s = max(1, min(s, nks / 8));
-        s = min(s, 64);
-    }
-    *ks_per_split = (nks + s - 1) / s;
-    *splits = (nks + *ks_per_split - 1) / *ks_per_split;
-    if (*splits < 1) *splits = 1;
+    const bool silu = g.epilogue == GEMM_EPI_BIAS_SILU;
+    if (silu && g.K <= 768) return true;
+    const long long gain = silu || g.K >= 2048 ? 125 : 110;
+    return gain * rounds(mb * nb_narrow) >= 200 * rounds(mb * nb);
+}
+
+void gemm_plan(GemmArgs* g) {
+    const long long mb = (g->M + GBM - 1) / GBM;
+    g->wide = use_wide(*g, mb, (g->N + 255) / 256, (g->N + GBN - 1) / GBN);
+    const int bn = g->wide ? 256 : GBN, bk = g->wide ? 64 : GBK;
+    g->mblocks = (int)mb;
+    g->nblocks = (int)((g->N + bn - 1) / bn);
+    g->splits = 1;
+    const long long tiles = (long long)g->mblocks * g->nblocks, nks = (g->K + bk - 1) / bk;
+    g->ks_per_split = (int)nks;
+    if (tiles == 0 || nks == 0 || g->layout != GEMM_TN) return;     // (an empty product launches nothing)
+    // enough workgroups for the chip (one per CU of the wide kernel, two of the narrow one), each
+    // split at least 8 k steps
+    const long long target = g->wide ? 256 / tiles : (512 + tiles - 1) / tiles;
+    const int s = (int)max(1ll, min(min(target, nks / 8), 64ll));
+    g->ks_per_split = (int)((nks + s - 1) / s);
+    g->splits = (int)((nks + g->ks_per_split - 1) / g->ks_per_split);
 }
 
 size_t gemm_workspace_bytes(int layout, long long M, long long N, long long K) {
     if (layout != GEMM_TN) return 0;
-    int mb, nb, s, per;
-    gemm_plan(layout, M, N, K, &mb, &nb, &s, &per);
-    return (size_t)s * (size_t)(M * N + N) * sizeof(float);
-}
-
-// Workgroups along x of the grid (see the block mapping in gemm_bf16_kernel).
-static int gemm_grid_x(int mblocks, int nblocks) {
-    if (mblocks >= XCDS) return XCDS * ((mblocks + XCDS - 1) / XCDS) * nblocks;
-    const int r = XCDS / mblocks;
-    return XCDS * ((nblocks + r - 1) / r);
+    GemmArgs g{};
+    g.layout = layout;
+    g.M = M;
+    g.N = N;
+    g.K = K;
+    gemm_plan(&g);
+    return (size_t)g.splits * (size_t)(M * N + N) * sizeof(float);
 }
 
 template <int LAYOUT, int EPI, bool COLSUM>
 static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
-    const int gx = gemm_grid_x(g.mblocks, g.nblocks);
-    gemm_bf16_kernel<LAYOUT, EPI, COLSUM><<<dim3(gx, g.splits), 256, 0, s>>>(g);
+    const int share = (g.mblocks * g.nblocks * g.splits + XCDS - 1) / XCDS;
+    gemm_bf16_kernel<LAYOUT, EPI, COLSUM><<<XCDS * share, 256, 0, s>>>(g);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
     hipError_t e = hipSuccess;
+    if (g.wide && g.layout != GEMM_TN) return launch_gemm_wide(g, s);
     switch (g.layout) {
         case GEMM_NN:
             if (g.epilogue == GEMM_EPI_BIAS_SILU) e = gemm_launch<GEMM_NN, GEMM_EPI_BIAS_SILU, false>(g, s);
@@ -553,7 +563,8 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
             else e = gemm_launch<GEMM_NT, GEMM_EPI_NONE, false>(g, s);
             return e;
         case GEMM_TN:
-            e = g.colsum ? gemm_launch<GEMM_TN, GEMM_EPI_NONE, true>(g, s) : gemm_launch<GEMM_TN, GEMM_EPI_NONE, false>(g, s);
+            e = g.wide ? launch_gemm_wide(g, s)
+                : g.colsum ? gemm_launch<GEMM_TN, GEMM_EPI_NONE, true>(g, s) : gemm_launch<GEMM_TN, GEMM_EPI_NONE, false>(g, s);
             if (e != hipSuccess) return e;
             {
                 const int sums = (int)min((g.M * g.N / 4 + 255) / 256, 8192ll);

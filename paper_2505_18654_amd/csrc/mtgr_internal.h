@@ -136,12 +136,15 @@ struct GemmArgs {
     float* partial;           // TN: [splits][M][N] fp32 workspace
     float* colsum_partial;    // TN: [splits][N] fp32 workspace
     int mblocks, nblocks, splits, ks_per_split;
+    bool wide;                // 256 x 256 tiles, k steps of 64 (gemm_wide.hip)
 };
 hipError_t launch_clock_probe(int iters, int blocks, long long* out, hipStream_t s);
-void gemm_plan(int layout, long long M, long long N, long long K, int* mblocks, int* nblocks, int* splits,
-               int* ks_per_split);
+// Tiles, K splits and kernel of a product (mblocks .. wide of `g` from layout, M, N and K).
+void gemm_plan(GemmArgs* g);
 size_t gemm_workspace_bytes(int layout, long long M, long long N, long long K);
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_wide(const GemmArgs& g, hipStream_t s);      // the products with g.wide
+constexpr int WIDE_WORKGROUPS = 256;                                   // of its persistent NN / NT form: one per CU
 
 // Elementwise out = a + b (bf16 or fp32) on [rows, cols] with row strides.
 hipError_t launch_add(long long rows, int cols, bool bf16, const void* a, long long lda, const void* b,
