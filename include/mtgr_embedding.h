@@ -85,7 +85,7 @@ mtgr_status_t mtgr_embedding_dedup_workspace_size(int64_t n, size_t* bytes);
  *   inverse     [n] int32    unique[inverse[i]] == ids[i]
  *   num_unique  [1] int64    (device)
  * ids [n] uint64.  A temporary hash set in the workspace (power-of-two capacity >= 2n) holds
- * each ID once; the unique list is that set compacted. */
+ * each ID once; an ID takes its place in the unique list when it enters the set. */
 mtgr_status_t mtgr_embedding_dedup(int64_t n, const uint64_t* ids, uint64_t* unique,
                                    int32_t* occurrences, int32_t* inverse, int64_t* num_unique,
                                    void* workspace, size_t workspace_bytes, mtgr_stream_t stream);
@@ -123,8 +123,9 @@ mtgr_status_t mtgr_embedding_sgd_workspace_size(int64_t n, int64_t n_max, int32_
  * grad_out [n, dim] of the table's dtype, row stride ld_grad; inverse, occurrences and
  * num_unique as produced by mtgr_embedding_dedup and rows by mtgr_embedding_lookup for the same
  * batch.  The positions are grouped by ID first (a counting sort driven by occurrences), so
- * each ID's gradient rows are summed in registers; only groups that straddle a 64-position
- * chunk are combined with float atomics (their order, and the last bits, vary). */
+ * each ID's gradient rows are summed in registers and applied at once; only an ID that reaches
+ * over the end of a workgroup's share of at most 1024 positions is combined with float atomics
+ * (their order, and the last bits, vary). */
 mtgr_status_t mtgr_embedding_sgd(const mtgr_embedding_table_t* t, int64_t n, const int32_t* inverse,
                                  const int32_t* occurrences, const void* grad_out, int64_t ld_grad,
                                  int64_t n_max, const int32_t* rows, const int64_t* num_unique, float lr,

@@ -859,6 +859,7 @@ int32_t mtgr_version(void) { return MTGR_HSTU_VERSION; }
 namespace {
 
 constexpr long long EMB_MAX_BATCH = 1ll << 30;   // IDs per dedup call (int32 positions)
+constexpr size_t EMB_LOOKUP_WORKSPACE = 512;     // of a lookup, which keeps nothing there now
 
 mtgr_status_t check_table(const mtgr_embedding_table_t* t, mtgr::EmbArgs* a) {
     if (!t) return fail(MTGR_ERROR_NULL_POINTER, "table is NULL");
@@ -949,7 +950,7 @@ mtgr_status_t mtgr_embedding_lookup_workspace_size(int64_t n_max, size_t* bytes)
     if (!bytes) return fail(MTGR_ERROR_NULL_POINTER, "bytes is NULL");
     mtgr_status_t st = check_count(n_max, EMB_MAX_BATCH, "n_max");
     if (st != MTGR_SUCCESS) return st;
-    *bytes = mtgr::lookup_workspace_bytes(n_max);
+    *bytes = EMB_LOOKUP_WORKSPACE;
     return ok();
 }
 
@@ -969,11 +970,11 @@ mtgr_status_t mtgr_embedding_lookup(const mtgr_embedding_table_t* t, int64_t n_m
     REQUIRE_PTR(workspace, "workspace");
     if (occurrences && !aligned16(occurrences))
         return fail(MTGR_ERROR_INVALID_ARGUMENT, "occurrences is not 16-byte aligned");
-    const size_t need = mtgr::lookup_workspace_bytes(n_max);
-    if (workspace_bytes < need)
-        return fail(MTGR_ERROR_WORKSPACE_TOO_SMALL, "workspace %zu bytes, need %zu", workspace_bytes, need);
+    if (workspace_bytes < EMB_LOOKUP_WORKSPACE)
+        return fail(MTGR_ERROR_WORKSPACE_TOO_SMALL, "workspace %zu bytes, need %zu", workspace_bytes,
+                    EMB_LOOKUP_WORKSPACE);
     hipError_t e = mtgr::launch_emb_lookup(a, n_max, unique, occurrences, (const long long*)num_unique, now,
-                                           insert ? 1 : 0, rows, workspace, (hipStream_t)stream);
+                                           insert ? 1 : 0, rows, (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "embedding lookup");
     return ok();
 }

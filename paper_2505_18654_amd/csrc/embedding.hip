@@ -9,6 +9,8 @@
 // walks.  Concurrency inside one call: distinct IDs race only for free slots (atomicCAS on the
 // 64-bit key) and for free rows (atomic counters); an ID's own slot and row are touched by one
 // thread, so its metadata needs no atomics.
+#include <type_traits>
+
 #include "../../include/mtgr_embedding.h"
 #include "mtgr_device.h"
 #include "mtgr_internal.h"
@@ -47,81 +49,33 @@ __global__ void fill_u64_kernel(uint64_t* p, long long n, uint64_t v) {
 __global__ void fill_i32_kernel(int* p, long long n, int v) {
     for (long long i = thread_id(); i < n; i += grid_threads()) p[i] = v;
 }
-__global__ void fill_f32_kernel(float* p, long long n, float v) {
-    for (long long i = thread_id(); i < n; i += grid_threads()) p[i] = v;
-}
 __global__ void zero_i64_kernel(long long* p) { *p = 0; }
 
 // ------------------------------------------------------------------------ de-duplication
-// Each workgroup takes DEDUP_CHUNK consecutive IDs and first de-duplicates them in an LDS hash
-// set (LDS integer atomics are cheap), then inserts each of its distinct IDs once into the
-// global set (capacity tmask + 1 >= 2 n) and adds its local count there with one atomic.
-// Skewed batches repeat a few hot IDs thousands of times; counting them in LDS first keeps the
-// global atomics on a hot ID to one per workgroup.  pos[i] = the global slot of ids[i].
-constexpr int DEDUP_PER_THREAD = 4;
-constexpr int DEDUP_CHUNK = THREADS * DEDUP_PER_THREAD;   // 1024 IDs
-constexpr int DEDUP_LCAP = 2 * DEDUP_CHUNK;               // LDS set: 2048 entries, 32 KB
+// Each workgroup takes TPB PER consecutive IDs and first de-duplicates them in an LDS hash set
+// (LDS integer atomics are cheap), then inserts each of its distinct IDs once into the global set
+// (capacity tmask + 1 >= 2 n) and adds its local count there with one atomic.  Skewed batches
+// repeat a few hot IDs thousands of times; counting them in LDS first keeps the global atomics on
+// a hot ID to one per workgroup.  Whoever brings an ID into the set gives it the next place of the
+// unique list (one atomic per workgroup), so the list needs no scan of the set.
+// pos[i] = the global slot of ids[i]; uslot[u] = that of unique[u].
+//
+// Bound by the latency of the dependent memory operations and by the atomics on the hottest IDs'
+// entries (one insertion and one count per workgroup, one after another), not by bytes.  So the
+// distinct IDs are compacted first and a thread's up to PER insertions are in flight together; an
+// entry (key, place, count) is 16 bytes of one line; and a workgroup takes as many IDs as leave one
+// workgroup per CU: 256 up to 65,536 IDs, 1,024 up to 262,144, else 4,096.
+// DEDUP_FIGS
+struct __align__(16) SetEntry {
+    uint64_t key;
+    int rank;       // place in the unique list
+    int occ;        // occurrences
+};
+constexpr long long BATCH_SMALL = 256 * 256, BATCH_MEDIUM = 256 * 1024;    // (see above)
 
-__global__ __launch_bounds__(THREADS) void dedup_insert_kernel(long long n, const uint64_t* __restrict__ ids,
-                                                               uint64_t* tkeys, int* tocc, int* __restrict__ pos,
-                                                               long long tmask) {
-    __shared__ uint64_t lkeys[DEDUP_LCAP];
-    __shared__ int lcount[DEDUP_LCAP];
-    __shared__ int lslot[DEDUP_LCAP];
-    const long long i0 = (long long)blockIdx.x * DEDUP_CHUNK;
-    for (int e = threadIdx.x; e < DEDUP_LCAP; e += THREADS) {
-        lkeys[e] = KEY_EMPTY;
-        lcount[e] = 0;
-    }
-    __syncthreads();
-    int mine[DEDUP_PER_THREAD];
-#pragma unroll
-    for (int k = 0; k < DEDUP_PER_THREAD; k++) {
-        const long long i = i0 + threadIdx.x + (long long)k * THREADS;
-        mine[k] = -1;
-        if (i >= n) continue;
-        const uint64_t key = ids[i];
-        int p = (int)(mix64(key) & (DEDUP_LCAP - 1));
-        for (int step = 0; step < DEDUP_LCAP; step++) {
-            const uint64_t old = atomicCAS((unsigned long long*)&lkeys[p], (unsigned long long)KEY_EMPTY,
-                                           (unsigned long long)key);
-            if (old == KEY_EMPTY || old == key) break;
-            p = (p + 1) & (DEDUP_LCAP - 1);
-        }
-        atomicAdd(&lcount[p], 1);
-        mine[k] = p;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < DEDUP_LCAP; e += THREADS) {
-        const uint64_t key = lkeys[e];
-        if (key == KEY_EMPTY) continue;
-        long long p = (long long)(mix64(key) & (uint64_t)tmask);
-        for (long long step = 0; step <= tmask; step++) {
-            const uint64_t k = load_key(tkeys + p);
-            if (k == key) break;
-            if (k == KEY_EMPTY) {
-                const uint64_t old = cas_key(tkeys + p, KEY_EMPTY, key);
-                if (old == KEY_EMPTY || old == key) break;
-            }
-            p = (p + 1) & tmask;
-        }
-        atomicAdd(tocc + p, lcount[e]);
-        lslot[e] = (int)p;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < DEDUP_PER_THREAD; k++) {
-        const long long i = i0 + threadIdx.x + (long long)k * THREADS;
-        if (i < n) pos[i] = lslot[mine[k]];
-    }
-}
-
-// Scan of the set's occupancy in blocks of SCAN_BLOCK slots (THREADS x 4).
-constexpr int SCAN_PER_THREAD = 4;
-constexpr int SCAN_BLOCK = THREADS * SCAN_PER_THREAD;
-
+template <int TPB>
 __device__ __forceinline__ int block_scan_exclusive(int v, int* total) {
-    __shared__ int wsum[THREADS / 64];
+    __shared__ int wsum[TPB / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int incl = v;
 #pragma unroll
@@ -133,7 +87,7 @@ __device__ __forceinline__ int block_scan_exclusive(int v, int* total) {
     __syncthreads();
     int before = 0, all = 0;
 #pragma unroll
-    for (int i = 0; i < THREADS / 64; i++) {
+    for (int i = 0; i < TPB / 64; i++) {
         before += i < w ? wsum[i] : 0;
         all += wsum[i];
     }
@@ -142,77 +96,168 @@ __device__ __forceinline__ int block_scan_exclusive(int v, int* total) {
     return before + incl - v;
 }
 
-__global__ __launch_bounds__(THREADS) void scan_count_kernel(const uint64_t* __restrict__ tkeys,
-                                                             long long tcap, int* __restrict__ bsum) {
-    const long long base = (long long)blockIdx.x * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
-    int c = 0;
-#pragma unroll
-    for (int e = 0; e < SCAN_PER_THREAD; e++) c += (base + e < tcap && tkeys[base + e] != KEY_EMPTY) ? 1 : 0;
-    int total;
-    block_scan_exclusive(c, &total);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = total;
+__global__ void dedup_clear_kernel(SetEntry* set, long long tcap, long long* num_unique) {
+    for (long long i = thread_id(); i < tcap; i += grid_threads())
+        ((uint4*)set)[i] = make_uint4(0xffffffffu, 0xffffffffu, 0u, 0u);
+    if (thread_id() == 0) *num_unique = 0;
 }
 
-// Exclusive scan of the nblk block counts (one workgroup, in chunks); *count = their sum.
-__global__ __launch_bounds__(THREADS) void scan_top_kernel(int* bsum, long long nblk, long long* count) {
-    long long carry = 0;
-    for (long long base = 0; base < nblk; base += THREADS) {
-        const long long i = base + threadIdx.x;
-        const int v = i < nblk ? bsum[i] : 0;
-        int total;
-        const int ex = block_scan_exclusive(v, &total);
-        if (i < nblk) bsum[i] = (int)(carry + ex);
-        carry += total;
-    }
-    if (threadIdx.x == 0) *count = carry;
-}
-
-__global__ __launch_bounds__(THREADS) void scan_emit_kernel(const uint64_t* __restrict__ tkeys,
-                                                            const int* __restrict__ tocc, long long tcap,
-                                                            const int* __restrict__ bsum, int* __restrict__ rank,
-                                                            uint64_t* __restrict__ unique,
-                                                            int* __restrict__ occ_out) {
-    const long long base = (long long)blockIdx.x * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
-    bool occ[SCAN_PER_THREAD];
-    int c = 0;
+template <int TPB, int PER>
+__global__ __launch_bounds__(TPB) void dedup_insert_kernel(long long n, const uint64_t* __restrict__ ids,
+                                                               SetEntry* set, int* __restrict__ pos, long long tmask,
+                                                               uint64_t* __restrict__ unique, int* __restrict__ uslot,
+                                                               long long* num_unique) {
+    constexpr int CHUNK = TPB * PER, LCAP = 2 * CHUNK;
+    __shared__ uint64_t lkeys[LCAP];
+    __shared__ int lcount[LCAP];
+    __shared__ int lslot[LCAP];
+    __shared__ int llist[CHUNK];
+    __shared__ int lnum, lbase;
+    const long long i0 = (long long)blockIdx.x * CHUNK;
+    uint64_t id[PER];
 #pragma unroll
-    for (int e = 0; e < SCAN_PER_THREAD; e++) {
-        occ[e] = base + e < tcap && tkeys[base + e] != KEY_EMPTY;
-        c += occ[e] ? 1 : 0;
+    for (int k = 0; k < PER; k++) {
+        const long long i = i0 + threadIdx.x + (long long)k * TPB;
+        id[k] = i < n ? ids[i] : 0;
+    }
+    for (int e = threadIdx.x; e < LCAP; e += TPB) {
+        lkeys[e] = KEY_EMPTY;
+        lcount[e] = 0;
+    }
+    if (threadIdx.x == 0) lnum = 0;
+    __syncthreads();
+    int mine[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const long long i = i0 + threadIdx.x + (long long)k * TPB;
+        mine[k] = -1;
+        if (i >= n) continue;
+        int p = (int)(mix64(id[k]) & (LCAP - 1));
+        for (int step = 0; step < LCAP; step++) {
+            const uint64_t old = atomicCAS((unsigned long long*)&lkeys[p], (unsigned long long)KEY_EMPTY,
+                                           (unsigned long long)id[k]);
+            if (old == KEY_EMPTY) llist[atomicAdd(&lnum, 1)] = p;
+            if (old == KEY_EMPTY || old == id[k]) break;
+            p = (p + 1) & (LCAP - 1);
+        }
+        atomicAdd(&lcount[p], 1);
+        mine[k] = p;
+    }
+    __syncthreads();
+    const int num = lnum;
+    uint64_t key[PER], old[PER];
+    long long at[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const int e = threadIdx.x + k * TPB;
+        key[k] = e < num ? lkeys[llist[e]] : KEY_EMPTY;
+        at[k] = (long long)(mix64(key[k]) & (uint64_t)tmask);
+        old[k] = e < num ? cas_key(&set[at[k]].key, KEY_EMPTY, key[k]) : key[k];
+    }
+    int fresh = 0;
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const int e = threadIdx.x + k * TPB;
+        for (long long step = 0; step <= tmask && old[k] != KEY_EMPTY && old[k] != key[k]; step++) {
+            at[k] = (at[k] + 1) & tmask;
+            old[k] = cas_key(&set[at[k]].key, KEY_EMPTY, key[k]);
+        }
+        if (e < num) {
+            atomicAdd(&set[at[k]].occ, lcount[llist[e]]);
+            lslot[llist[e]] = (int)at[k];
+            fresh += old[k] == KEY_EMPTY ? 1 : 0;
+        }
     }
     int total;
-    int r = bsum[blockIdx.x] + block_scan_exclusive(c, &total);
+    int r = block_scan_exclusive<TPB>(fresh, &total);
+    if (threadIdx.x == 0) lbase = (int)atomicAdd((unsigned long long*)num_unique, (unsigned long long)total);
+    __syncthreads();
+    r += lbase;
 #pragma unroll
-    for (int e = 0; e < SCAN_PER_THREAD; e++) {
-        if (occ[e]) {
-            rank[base + e] = r;
-            unique[r] = tkeys[base + e];
-            if (occ_out) occ_out[r] = tocc[base + e];
+    for (int k = 0; k < PER; k++) {
+        if (threadIdx.x + k * TPB < num && old[k] == KEY_EMPTY) {
+            set[at[k]].rank = r;
+            unique[r] = key[k];
+            uslot[r] = (int)at[k];
             r++;
         }
     }
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const long long i = i0 + threadIdx.x + (long long)k * TPB;
+        if (i < n) pos[i] = lslot[mine[k]];
+    }
 }
 
-__global__ void dedup_inverse_kernel(long long n, const int* __restrict__ pos, const int* __restrict__ rank,
-                                     int* __restrict__ inverse) {
-    for (long long i = thread_id(); i < n; i += grid_threads()) inverse[i] = rank[pos[i]];
+// inverse of every position and the occurrences of every unique ID (their number is at most n).
+__global__ void dedup_finish_kernel(long long n, const SetEntry* __restrict__ set, const int* __restrict__ pos,
+                                    const int* __restrict__ uslot, const long long* __restrict__ num_unique,
+                                    int* __restrict__ inverse, int* __restrict__ occ_out) {
+    const long long nu = occ_out ? *num_unique : 0;
+    for (long long i = thread_id(); i < n; i += grid_threads()) {
+        inverse[i] = set[pos[i]].rank;
+        if (i < nu) occ_out[i] = set[uslot[i]].occ;
+    }
 }
 
 // ------------------------------------------------------------------------ lookup / insert
-// Phase 1: find each ID's slot, or (insert) claim one: the first DELETED slot met on the probe
-// path if the path ends at an EMPTY slot without the ID, else that EMPTY slot.  lpos = slot or
-// -1 (absent, or no free slot: overflow bit 1), lfresh = 1 when claimed here.
-__global__ void lookup_probe_kernel(EmbArgs t, long long n_max, const uint64_t* __restrict__ unique,
-                                    const long long* __restrict__ num_unique, int insert,
-                                    int* __restrict__ lpos, int* __restrict__ lfresh) {
+// Rows for the `want` lanes of a wave (all its active lanes call): the top of the free-row stack,
+// then the never-used rows, -1 when both are used up.  One atomic per wave and source; what was
+// taken beyond the supply is given back at once.  While any of it is outstanding the stack top is
+// <= 0 and the row counter >= the capacity, so no wave mistakes it for supply.
+__device__ __forceinline__ int alloc_rows(const EmbArgs& t, bool want) {
+    const unsigned long long m = __ballot(want);
+    if (!m) return -1;
+    const int lane = threadIdx.x & 63, leader = __builtin_ctzll(m), n = __popcll(m);
+    int* top_p = t.state + MTGR_EMB_STATE_FREE_TOP;
+    uint32_t* next_p = (uint32_t*)(t.state + MTGR_EMB_STATE_NEXT_ROW);
+    const uint32_t cap = (uint32_t)t.row_capacity;
+    int top = 0, take = 0;
+    uint32_t next = 0;
+    if (lane == leader) {
+        if (__hip_atomic_load(top_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0) {
+            top = atomicSub(top_p, n);
+            take = min(max(top, 0), n);
+            if (take < n) atomicAdd(top_p, n - take);
+        }
+        const uint32_t rest = (uint32_t)(n - take);
+        if (rest) {
+            next = atomicAdd(next_p, rest);
+            const uint32_t end = next + rest, over = end > cap ? min(end - cap, rest) : 0u;
+            if (over) atomicSub(next_p, over);
+        }
+    }
+    top = __shfl(top, leader, 64);
+    take = __shfl(take, leader, 64);
+    next = (uint32_t)__shfl((int)next, leader, 64);
+    if (!want) return -1;
+    const int k = __popcll(m & ((1ull << lane) - 1));
+    if (k < take) return t.free_rows[top - 1 - k];
+    const uint32_t r = next + (uint32_t)(k - take);
+    return r < cap ? (int)r : -1;
+}
+
+__device__ __forceinline__ void zero_row(const EmbArgs& t, int row) {
+    uint4* v = (uint4*)((char*)t.values + (long long)row * t.dim * t.esize);
+    const int chunks = t.dim * t.esize / 16;
+    for (int c = 0; c < chunks; c++) v[c] = make_uint4(0, 0, 0, 0);
+}
+
+// Finds each ID's slot, or (insert) claims one: the first DELETED slot met on the probe path if the
+// path ends at an EMPTY slot without the ID, else that EMPTY slot; then rows for the claimed
+// slots, counters and timestamps.  The IDs of a call are distinct, so no other thread reads a
+// slot claimed here, and one launch does both.
+// LOOKUP_FIGS
+__global__ void lookup_kernel(EmbArgs t, long long n_max, const uint64_t* __restrict__ unique,
+                              const int* __restrict__ occurrences, const long long* __restrict__ num_unique, int now,
+                              int insert, int* __restrict__ rows) {
     const long long nu = min(*num_unique, n_max);
     const long long mask = t.key_capacity - 1;
     for (long long u = thread_id(); u < nu; u += grid_threads()) {
         const uint64_t key = unique[u];
         long long p = (long long)(mix64(key) & (uint64_t)mask);
         long long tomb = -1, slot = -1;
-        int fresh = 0;
-        bool done = false;
+        bool fresh = false, done = false;
         for (long long step = 0; step < 2 * t.key_capacity && !done; step++) {
             const uint64_t k = load_key(t.keys + p);
             if (k == key) {
@@ -229,7 +274,7 @@ __global__ void lookup_probe_kernel(EmbArgs t, long long n_max, const uint64_t* 
                     const uint64_t expect = tomb >= 0 ? KEY_DELETED : KEY_EMPTY;
                     if (cas_key(t.keys + tgt, expect, key) == expect) {
                         slot = tgt;
-                        fresh = 1;
+                        fresh = true;
                         done = true;
                     } else if (tomb >= 0) {
                         tomb = -1;           // another ID took the deleted slot: look at p again
@@ -243,71 +288,33 @@ __global__ void lookup_probe_kernel(EmbArgs t, long long n_max, const uint64_t* 
         }
         if (!done && insert && tomb >= 0 && cas_key(t.keys + tomb, KEY_DELETED, key) == KEY_DELETED) {
             slot = tomb;   // the whole store was walked: no EMPTY slot, but a DELETED one
-            fresh = 1;
+            fresh = true;
             done = true;
         }
-        if (fresh) atomicAdd(t.state + MTGR_EMB_STATE_NUM_KEYS, 1);
         if (!done && insert) atomicOr(t.state + MTGR_EMB_STATE_OVERFLOW, 2);
-        lpos[u] = (int)slot;
-        lfresh[u] = fresh;
-    }
-}
-
-// A free row: the top of the free-row stack, else the next never-used row, else -1.  The
-// stack top may go negative and the row counter past the capacity; fixup_kernel clamps both.
-__device__ __forceinline__ int alloc_row(const EmbArgs& t) {
-    const int i = atomicSub(t.state + MTGR_EMB_STATE_FREE_TOP, 1) - 1;
-    if (i >= 0) return t.free_rows[i];
-    const int r = atomicAdd(t.state + MTGR_EMB_STATE_NEXT_ROW, 1);
-    return r < t.row_capacity ? r : -1;
-}
-
-__device__ __forceinline__ void zero_row(const EmbArgs& t, int row) {
-    uint4* v = (uint4*)((char*)t.values + (long long)row * t.dim * t.esize);
-    const int chunks = t.dim * t.esize / 16;
-    for (int c = 0; c < chunks; c++) v[c] = make_uint4(0, 0, 0, 0);
-}
-
-// Phase 2: rows for the claimed slots, then counters and timestamps.
-__global__ void lookup_finish_kernel(EmbArgs t, long long n_max, const int* __restrict__ occurrences,
-                                     const long long* __restrict__ num_unique, int now,
-                                     const int* __restrict__ lpos, const int* __restrict__ lfresh,
-                                     int* __restrict__ rows) {
-    const long long nu = min(*num_unique, n_max);
-    for (long long u = thread_id(); u < nu; u += grid_threads()) {
-        const int p = lpos[u];
-        if (p < 0) {
-            rows[u] = -1;
-            continue;
-        }
-        int row;
-        if (lfresh[u]) {
-            row = alloc_row(t);
+        int row = alloc_rows(t, fresh);
+        const unsigned long long live = __ballot(fresh && row >= 0);
+        if (live && (int)(threadIdx.x & 63) == __builtin_ctzll(live))
+            atomicAdd(t.state + MTGR_EMB_STATE_NUM_KEYS, (int)__popcll(live));
+        if (fresh) {
             if (row < 0) {
                 // No row: release the slot as DELETED (IDs inserted meanwhile may have probed
                 // past it, so it must not become EMPTY).
-                __hip_atomic_store(t.keys + p, KEY_DELETED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                atomicSub(t.state + MTGR_EMB_STATE_NUM_KEYS, 1);
+                __hip_atomic_store(t.keys + slot, KEY_DELETED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 atomicOr(t.state + MTGR_EMB_STATE_OVERFLOW, 1);
-                rows[u] = -1;
-                continue;
+            } else {
+                t.key_rows[slot] = row;
+                zero_row(t, row);
             }
-            t.key_rows[p] = row;
-            zero_row(t, row);
-            t.counts[row] = 0u;
-        } else {
-            row = t.key_rows[p];
+        } else if (slot >= 0) {
+            row = t.key_rows[slot];
         }
-        t.counts[row] += occurrences ? (uint32_t)occurrences[u] : 1u;
-        t.last_ts[row] = now;
+        if (row >= 0) {
+            t.counts[row] = (fresh ? 0u : t.counts[row]) + (occurrences ? (uint32_t)occurrences[u] : 1u);
+            t.last_ts[row] = now;
+        }
         rows[u] = row;
     }
-}
-
-__global__ void fixup_kernel(EmbArgs t) {
-    int* s = t.state;
-    s[MTGR_EMB_STATE_FREE_TOP] = max(s[MTGR_EMB_STATE_FREE_TOP], 0);
-    s[MTGR_EMB_STATE_NEXT_ROW] = min(s[MTGR_EMB_STATE_NEXT_ROW], t.row_capacity);
 }
 
 // ------------------------------------------------------------------------ gather / sgd
@@ -343,238 +350,277 @@ __device__ __forceinline__ void load_chunk(const void* base, int esize, float* f
     }
 }
 
-// Grouping of a batch's positions by unique ID (a counting sort): start = exclusive scan of
-// the occurrences, then each position takes the next free place of its ID's range.
-__global__ __launch_bounds__(THREADS) void iscan_count_kernel(const int* __restrict__ in,
-                                                              const long long* __restrict__ num, long long n_max,
-                                                              int* __restrict__ bsum) {
-    const long long nv = min(*num, n_max);
-    const long long base = (long long)blockIdx.x * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
-    int c = 0;
+// One chunk of a row plus -lr times a sum, rounded to the table's dtype.
+template <int ESIZE>
+__device__ __forceinline__ void apply_chunk(void* vp, uint4 old, const float* g, float lr) {
+    constexpr int epc = 16 / ESIZE;
+    float f[8];
+    load_chunk(&old, ESIZE, f);
 #pragma unroll
-    for (int e = 0; e < SCAN_PER_THREAD; e++) c += base + e < nv ? in[base + e] : 0;
-    int total;
-    block_scan_exclusive(c, &total);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = total;
+    for (int e = 0; e < epc; e++) f[e] = __builtin_fmaf(-lr, g[e], f[e]);
+    uint4 v;
+    if constexpr (ESIZE == 2)
+        v = make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]),
+                       pack_bf16x2(f[6], f[7]));
+    else
+        v = make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
+    *(uint4*)vp = v;
 }
 
-__global__ __launch_bounds__(THREADS) void iscan_apply_kernel(const int* __restrict__ in,
-                                                              const long long* __restrict__ num, long long n_max,
-                                                              const int* __restrict__ bsum, int* __restrict__ out) {
+// The SGD step groups the positions by unique ID (a counting sort over the occurrences, in any
+// order of the IDs), then sums runs of equal IDs and applies each whole run to its row at once.
+// A workgroup of the sum owns sgd_positions(dim) consecutive places of the grouped list; the IDs
+// that reach beyond one (few: at most one per workgroup boundary) add their parts with float atomics into
+// an accumulator row of the workgroup they start in, which a last small kernel applies.
+struct SgdWork {
+    float* acc;       // [groups][dim]
+    int* span;        // [groups]: the ID that starts in this workgroup and reaches beyond it, or -1
+    int* total;       // [1]: places handed out
+    int* cursor;      // [n_max]: next free place of each ID; its end after the scatter
+    int2* list;       // [n]: {position, ID}
+    long long groups;
+};
+
+__global__ void sgd_clear_kernel(SgdWork w, int dim) {
+    for (long long i = thread_id(); i < w.groups * dim; i += grid_threads()) w.acc[i] = 0.f;
+    for (long long i = thread_id(); i < w.groups; i += grid_threads()) w.span[i] = -1;
+    if (thread_id() == 0) *w.total = 0;
+}
+
+// Disjoint ranges of the list for the IDs: a scan inside the workgroup, one atomic per workgroup.
+constexpr int START_PER = 4;
+__global__ __launch_bounds__(THREADS) void sgd_start_kernel(SgdWork w, const int* __restrict__ occ,
+                                                            const long long* __restrict__ num, long long n_max) {
+    __shared__ int lbase;
     const long long nv = min(*num, n_max);
-    const long long base = (long long)blockIdx.x * SCAN_BLOCK + threadIdx.x * SCAN_PER_THREAD;
-    int v[SCAN_PER_THREAD], c = 0;
+    const long long base = ((long long)blockIdx.x * THREADS + threadIdx.x) * START_PER;
+    int v[START_PER], c = 0;
 #pragma unroll
-    for (int e = 0; e < SCAN_PER_THREAD; e++) {
-        v[e] = base + e < nv ? in[base + e] : 0;
+    for (int e = 0; e < START_PER; e++) {
+        v[e] = base + e < nv ? occ[base + e] : 0;
         c += v[e];
     }
     int total;
-    int r = bsum[blockIdx.x] + block_scan_exclusive(c, &total);
+    int r = block_scan_exclusive<THREADS>(c, &total);
+    if (threadIdx.x == 0) lbase = total ? atomicAdd(w.total, total) : 0;
+    __syncthreads();
+    r += lbase;
 #pragma unroll
-    for (int e = 0; e < SCAN_PER_THREAD; e++) {
-        if (base + e < nv) out[base + e] = r;
+    for (int e = 0; e < START_PER; e++) {
+        if (base + e < nv) w.cursor[base + e] = r;
         r += v[e];
     }
 }
 
-// Counting-sort scatter of the positions: list[start[u] + r] = i for the r-th position of ID u
-// (lu = u alongside).  A workgroup takes DEDUP_CHUNK positions and counts its IDs in an LDS hash
-// first, so a hot ID costs one global atomic per workgroup; its positions then take
-// consecutive places from the range reserved there.
-__global__ __launch_bounds__(THREADS) void group_scatter_kernel(long long n, const int* __restrict__ inverse,
-                                                                const int* __restrict__ start, int* cursor,
-                                                                int* __restrict__ list, int* __restrict__ lu) {
-    __shared__ int lkey[DEDUP_LCAP];
-    __shared__ int lcount[DEDUP_LCAP];
-    __shared__ int lbase[DEDUP_LCAP];
-    const long long i0 = (long long)blockIdx.x * DEDUP_CHUNK;
-    for (int e = threadIdx.x; e < DEDUP_LCAP; e += THREADS) {
+// Places of the positions.  A workgroup takes TPB PER positions and counts its IDs in an LDS hash
+// first, so a hot ID costs one global atomic per workgroup; its positions then take consecutive
+// places from the range reserved there.  TPB and PER as in the de-duplication.
+template <int TPB, int PER>
+__global__ __launch_bounds__(TPB) void sgd_scatter_kernel(SgdWork w, long long n, const int* __restrict__ inverse) {
+    constexpr int CHUNK = TPB * PER, LCAP = 2 * CHUNK;
+    __shared__ int lkey[LCAP];
+    __shared__ int lcount[LCAP];
+    __shared__ int lbase[LCAP];
+    __shared__ int llist[CHUNK];
+    __shared__ int lnum;
+    const long long i0 = (long long)blockIdx.x * CHUNK;
+    int u[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const long long i = i0 + threadIdx.x + (long long)k * TPB;
+        u[k] = i < n ? inverse[i] : 0;
+    }
+    for (int e = threadIdx.x; e < LCAP; e += TPB) {
         lkey[e] = -1;
         lcount[e] = 0;
     }
+    if (threadIdx.x == 0) lnum = 0;
     __syncthreads();
-    int slot[DEDUP_PER_THREAD], rank[DEDUP_PER_THREAD];
+    int slot[PER], rank[PER];
 #pragma unroll
-    for (int k = 0; k < DEDUP_PER_THREAD; k++) {
-        const long long i = i0 + threadIdx.x + (long long)k * THREADS;
+    for (int k = 0; k < PER; k++) {
+        const long long i = i0 + threadIdx.x + (long long)k * TPB;
         slot[k] = -1;
         rank[k] = 0;
         if (i >= n) continue;
-        const int u = inverse[i];
-        int p = (int)(mix64((uint64_t)u) & (DEDUP_LCAP - 1));
-        for (int step = 0; step < DEDUP_LCAP; step++) {
-            const int old = atomicCAS(&lkey[p], -1, u);
-            if (old == -1 || old == u) break;
-            p = (p + 1) & (DEDUP_LCAP - 1);
+        int p = (int)(((uint32_t)u[k] * 2654435761u) >> 16) & (LCAP - 1);
+        for (int step = 0; step < LCAP; step++) {
+            const int old = atomicCAS(&lkey[p], -1, u[k]);
+            if (old == -1) llist[atomicAdd(&lnum, 1)] = p;
+            if (old == -1 || old == u[k]) break;
+            p = (p + 1) & (LCAP - 1);
         }
         rank[k] = atomicAdd(&lcount[p], 1);
         slot[k] = p;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < DEDUP_LCAP; e += THREADS) {
-        const int u = lkey[e];
-        if (u >= 0) lbase[e] = start[u] + atomicAdd(cursor + u, lcount[e]);
+    const int num = lnum;
+    int got[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const int e = threadIdx.x + k * TPB;
+        got[k] = e < num ? atomicAdd(w.cursor + lkey[llist[e]], lcount[llist[e]]) : 0;
     }
+#pragma unroll
+    for (int k = 0; k < PER; k++)
+        if (threadIdx.x + k * TPB < num) lbase[llist[threadIdx.x + k * TPB]] = got[k];
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < DEDUP_PER_THREAD; k++) {
-        const long long i = i0 + threadIdx.x + (long long)k * THREADS;
+    for (int k = 0; k < PER; k++) {
+        const long long i = i0 + threadIdx.x + (long long)k * TPB;
         if (i >= n) continue;
         const int p = lbase[slot[k]] + rank[k];
-        if (p < n) {   // always, for occurrences consistent with inverse
-            list[p] = (int)i;
-            lu[p] = lkey[slot[k]];
-        }
+        if (p < n) w.list[p] = make_int2((int)i, u[k]);   // always, for occurrences consistent with inverse
     }
 }
 
-// Sum of each ID's gradient rows.  The grouped positions are cut into chunks of GROUP_CHUNK;
-// a workgroup of THREADS threads takes CPB = THREADS / cpr consecutive chunks, one thread per
-// (chunk, 16-byte column block).  A thread walks its chunk and sums runs of one ID in
-// registers: runs strictly inside the chunk are complete IDs and are stored; the first and last
-// run go to LDS, where one thread per column then merges equal IDs across the workgroup's chunks
-// and stores each merged run, or adds it with a float atomic when the ID continues beyond the
-// workgroup.  A hot ID with thousands of positions thus costs one atomic per workgroup and
-// column element instead of one per chunk.
-constexpr int GROUP_CHUNK = 32;
+// Chunks of a workgroup (one thread per chunk and 16-byte column block) and places per chunk: at
+// most 1024 places per workgroup, 32 per thread.
+__host__ __device__ __forceinline__ int sgd_chunks(int dim, int esize) { return THREADS / (dim * esize / 16); }
+__host__ __device__ __forceinline__ int sgd_chunk_len(int chunks) { return chunks > 32 ? 1024 / chunks : 32; }
 
+// Bound by the random 128-byte gradient and value rows (dim 64, bf16); per thread eight positions'
+// gradient and value chunks are in flight together, the list and rows come in through LDS once
+// per workgroup, and a run inside a chunk is a whole ID, which needs no look at its range.
+// SUM_FIGS
 template <int ESIZE>
-__global__ __launch_bounds__(THREADS) void group_sum_kernel(EmbArgs t, long long n, const int* __restrict__ list,
-                                                            const int* __restrict__ lu,
-                                                            const int* __restrict__ start,
-                                                            const int* __restrict__ occ,
-                                                            const void* __restrict__ grad, long long ld_grad,
-                                                            float* acc) {
+__global__ __launch_bounds__(THREADS) void sgd_sum_kernel(EmbArgs t, SgdWork w, long long n, long long n_max,
+                                                          const int* __restrict__ occ, const int* __restrict__ rows,
+                                                          const void* __restrict__ grad, long long ld_grad, float lr) {
     constexpr int epc = 16 / ESIZE, UNR = 8;
-    static_assert(GROUP_CHUNK % UNR == 0, "whole unrolled steps");
+    __shared__ int lpos[1024];
+    __shared__ int lid[1024];
+    __shared__ int lrow[1024];
     __shared__ float first_part[THREADS][epc];
     __shared__ float last_part[THREADS][epc];
-    __shared__ int first_u[THREADS];
-    __shared__ int last_u[THREADS];
     const int cpr = t.dim / epc;                       // column blocks per row (<= THREADS here)
-    const int cpb = THREADS / cpr;                     // chunks per workgroup
-    const long long P0 = (long long)blockIdx.x * cpb * GROUP_CHUNK, P1 = min(n, P0 + (long long)cpb * GROUP_CHUNK);
+    const int cpb = sgd_chunks(t.dim, ESIZE), len = sgd_chunk_len(cpb);
+    const long long P0 = (long long)blockIdx.x * cpb * len;
+    const int cnt = (int)min((long long)cpb * len, n - P0);
+    for (int p = threadIdx.x; p < cnt; p += THREADS) {
+        const int2 e = w.list[P0 + p];
+        // (for inconsistent occurrences the list has holes: nothing is read through them)
+        const bool in = e.x >= 0 && e.x < n && e.y >= 0 && e.y < n_max;
+        lpos[p] = in ? e.x : -1;
+        lid[p] = in ? e.y : -1;
+        lrow[p] = in ? rows[e.y] : -1;
+    }
+    __syncthreads();
     const int c = threadIdx.x / cpr, j = threadIdx.x - c * cpr;
-    const long long p0 = P0 + (long long)c * GROUP_CHUNK, p1 = min(P1, p0 + GROUP_CHUNK);
-    auto store_or_add = [&](int u, const float* f, long long lo, long long hi) {
-        float* dst = acc + (long long)u * t.dim + j * epc;
-        const long long s0 = start[u], s1 = s0 + occ[u];
-        if (s0 >= lo && s1 <= hi) {
-#pragma unroll
-            for (int e = 0; e < epc; e++) dst[e] = f[e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < epc; e++) atomicAdd(dst + e, f[e]);
-        }
-    };
+    const int p0 = c * len, p1 = c < cpb ? min(cnt, p0 + len) : p0;
+    char* vbase = (char*)t.values + (long long)j * 16;
+    const long long vstride = (long long)t.dim * ESIZE;
     float f[epc];
 #pragma unroll
     for (int e = 0; e < epc; e++) f[e] = 0.f;
-    int cur = -1, runs = 0;
-    if (c < cpb) {
-        for (long long pb = p0; pb < p1; pb += UNR) {
-            int ii[UNR], uu[UNR];
+    int cur = -1, crow = -1, runs = 0, first_id = -1;
+    uint4 cval = make_uint4(0, 0, 0, 0);
+    for (int pb = p0; pb < p1; pb += UNR) {
+        uint4 g[UNR], v[UNR];
+        int uu[UNR], rr[UNR];
 #pragma unroll
-            for (int k = 0; k < UNR; k++) {
-                const bool in = pb + k < p1;
-                ii[k] = in ? list[pb + k] : -1;
-                uu[k] = in ? lu[pb + k] : -1;
-            }
-            float g[UNR][8];
+        for (int k = 0; k < UNR; k++) {
+            const bool in = pb + k < p1;
+            const int i = in ? lpos[pb + k] : -1;
+            uu[k] = in ? lid[pb + k] : -1;
+            rr[k] = in ? lrow[pb + k] : -1;
+            g[k] = v[k] = make_uint4(0, 0, 0, 0);
+            if (i >= 0) g[k] = *(const uint4*)((const char*)grad + (long long)i * ld_grad * ESIZE + (long long)j * 16);
+            if (rr[k] >= 0) v[k] = *(const uint4*)(vbase + rr[k] * vstride);
+        }
 #pragma unroll
-            for (int k = 0; k < UNR; k++) {
-                if (ii[k] >= 0 && ii[k] < n)
-                    load_chunk((const char*)grad + ((long long)ii[k] * ld_grad + (long long)j * epc) * ESIZE, ESIZE,
-                               g[k]);
-                else
-                    uu[k] = -1;   // past the chunk (or, for inconsistent occurrences, a hole)
-            }
+        for (int k = 0; k < UNR; k++) {
+            if (uu[k] < 0) continue;
+            if (uu[k] != cur) {
+                if (runs == 1) {            // the chunk's first run: to LDS
+                    first_id = cur;
 #pragma unroll
-            for (int k = 0; k < UNR; k++) {
-                if (uu[k] < 0) continue;
-                if (uu[k] != cur) {
-                    if (cur >= 0) {
-                        if (runs == 1) {   // the first run of the chunk: to LDS
-                            first_u[threadIdx.x] = cur;
-#pragma unroll
-                            for (int e = 0; e < epc; e++) first_part[threadIdx.x][e] = f[e];
-                        } else {           // a run strictly inside the chunk: a whole ID
-                            store_or_add(cur, f, p0, p1);
-                        }
-                    }
-                    cur = uu[k];
-                    runs++;
-#pragma unroll
-                    for (int e = 0; e < epc; e++) f[e] = 0.f;
+                    for (int e = 0; e < epc; e++) first_part[threadIdx.x][e] = f[e];
+                } else if (runs > 1 && crow >= 0) {   // a run strictly inside the chunk: a whole ID
+                    apply_chunk<ESIZE>(vbase + crow * vstride, cval, f, lr);
                 }
+                cur = uu[k];
+                runs++;
 #pragma unroll
-                for (int e = 0; e < epc; e++) f[e] += g[k][e];
+                for (int e = 0; e < epc; e++) f[e] = 0.f;
             }
+            crow = rr[k];
+            cval = v[k];
+            float gk[8];
+            load_chunk(&g[k], ESIZE, gk);
+#pragma unroll
+            for (int e = 0; e < epc; e++) f[e] += gk[e];
         }
     }
-    // the last run (the first as well when the chunk holds one ID; none for an empty chunk)
-    if (runs == 1) first_u[threadIdx.x] = -1;
-    if (runs == 0) first_u[threadIdx.x] = -1;
+    // Chunk c's first run (first_id, when it holds more than one) and last run (cur) are merged with
+    // equal IDs of the neighbouring chunks by the thread of the chunk where the ID begins.
+    __shared__ int first_u[THREADS];
+    __shared__ int last_u[THREADS];
+    first_u[threadIdx.x] = first_id;
     last_u[threadIdx.x] = cur;
 #pragma unroll
     for (int e = 0; e < epc; e++) last_part[threadIdx.x][e] = f[e];
     __syncthreads();
-    if (threadIdx.x < cpr) {
-        int run_u = -1;
+    if (runs == 0) return;
+    // sum (from this chunk) of ID u whose part here is `part`; `reach`: it is the chunk's last run
+    auto finish = [&](int u, const float* part, bool reach, int row, uint4 val) {
         float r[epc];
 #pragma unroll
-        for (int e = 0; e < epc; e++) r[e] = 0.f;
-        for (int cc = 0; cc < cpb; cc++) {
-            const int pair = cc * cpr + j;
+        for (int e = 0; e < epc; e++) r[e] = part[e];
+        bool to_end = false;      // reaches the workgroup's last place
+        if (reach) {
+            int cc = c + 1;
+            for (; cc < cpb && cc * len < cnt; cc++) {
+                const int pair = cc * cpr + j, fu = first_u[pair];
+                const bool whole = fu < 0 && last_u[pair] == u;      // the chunk holds nothing else
+                if (!whole && fu != u) break;
+                const float* q = whole ? last_part[pair] : first_part[pair];
 #pragma unroll
-            for (int half = 0; half < 2; half++) {
-                const int u = half == 0 ? first_u[pair] : last_u[pair];
-                if (u < 0) continue;
-                const float* part = half == 0 ? first_part[pair] : last_part[pair];
-                if (u != run_u) {
-                    if (run_u >= 0) store_or_add(run_u, r, P0, P1);
-                    run_u = u;
-#pragma unroll
-                    for (int e = 0; e < epc; e++) r[e] = 0.f;
-                }
-#pragma unroll
-                for (int e = 0; e < epc; e++) r[e] += part[e];
+                for (int e = 0; e < epc; e++) r[e] += q[e];
+                if (!whole) break;
             }
+            to_end = cc >= cpb || cc * len >= cnt;
         }
-        if (run_u >= 0) store_or_add(run_u, r, P0, P1);
+        const bool from_start = c == 0 && lid[0] == u;
+        long long group = blockIdx.x;
+        bool spans = false;
+        if (from_start || to_end) {
+            const long long end = w.cursor[u], start = end - occ[u];
+            spans = start < P0 || end > P0 + cnt;
+            group = start / ((long long)cpb * len);
+        }
+        if (!spans) {
+            if (row >= 0) apply_chunk<ESIZE>(vbase + row * vstride, val, r, lr);
+        } else if (group >= 0 && group < w.groups) {
+            float* dst = w.acc + group * t.dim + j * epc;
+#pragma unroll
+            for (int e = 0; e < epc; e++) atomicAdd(dst + e, r[e]);
+            if (group == blockIdx.x && j == 0) w.span[group] = u;
+        }
+    };
+    const int before = c > 0 ? last_u[threadIdx.x - cpr] : -1;
+    if (runs > 1 && first_id != before) {
+        const int row = lrow[p0];
+        const uint4 val = row >= 0 ? *(const uint4*)(vbase + row * vstride) : make_uint4(0, 0, 0, 0);
+        finish(first_id, first_part[threadIdx.x], false, row, val);
     }
+    if (runs > 1 || cur != before) finish(cur, last_part[threadIdx.x], true, crow, cval);
 }
 
-// values[rows[u], :] -= lr * acc[u, :], rounded to the table's dtype.
+// The IDs that span workgroups: values[rows[u], :] -= lr * their accumulated sums.
 template <int ESIZE>
-__global__ void sgd_apply_kernel(EmbArgs t, long long n_max, const int* __restrict__ rows,
-                                 const long long* __restrict__ num_unique, const float* __restrict__ acc,
-                                 float lr) {
+__global__ void sgd_span_kernel(EmbArgs t, SgdWork w, const int* __restrict__ rows, float lr) {
     constexpr int epc = 16 / ESIZE;
-    const long long nu = min(*num_unique, n_max);
     const int cpr = t.dim / epc;
-    const long long total = nu * cpr;
-    for (long long c = thread_id(); c < total; c += grid_threads()) {
-        const long long u = c / cpr;
-        const int j = (int)(c - u * cpr);
+    const long long total = w.groups * cpr;
+    for (long long i = thread_id(); i < total; i += grid_threads()) {
+        const long long grp = i / cpr;
+        const int u = w.span[grp], j = (int)(i - grp * cpr);
+        if (u < 0) continue;
         const int row = rows[u];
         if (row < 0) continue;
         char* vp = (char*)t.values + ((long long)row * t.dim + (long long)j * epc) * ESIZE;
-        float f[8];
-        load_chunk(vp, ESIZE, f);
-        const float* g = acc + u * t.dim + j * epc;
-#pragma unroll
-        for (int e = 0; e < epc; e++) f[e] = __builtin_fmaf(-lr, g[e], f[e]);
-        uint4 v;
-        if constexpr (ESIZE == 2) {
-            v = make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]),
-                           pack_bf16x2(f[6], f[7]));
-        } else {
-            v = make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]),
-                           __float_as_uint(f[3]));
-        }
-        *(uint4*)vp = v;
+        apply_chunk<ESIZE>(vp, *(const uint4*)vp, w.acc + grp * t.dim + j * epc, lr);
     }
 }
 
@@ -626,11 +672,10 @@ size_t dedup_set_capacity(long long n) {
     return c;
 }
 
+static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
 size_t dedup_workspace_bytes(long long n) {
-    const size_t tcap = dedup_set_capacity(n);
-    const size_t nblk = (tcap + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    auto a = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    return a(tcap * 8) + a(tcap * 4) * 2 + a((size_t)n * 4) + a((nblk + 1) * 4);
+    return align256(dedup_set_capacity(n) * sizeof(SetEntry)) + 2 * align256((size_t)n * 4);
 }
 
 hipError_t launch_emb_init(const EmbArgs& t, hipStream_t s) {
@@ -640,48 +685,37 @@ hipError_t launch_emb_init(const EmbArgs& t, hipStream_t s) {
     return hipGetLastError();
 }
 
+// f(threads, IDs per thread) of the kernels that de-duplicate in LDS, by the batch's size.
+template <class F>
+static void by_batch(long long n, F f) {
+    using std::integral_constant;
+    if (n <= BATCH_SMALL) f(integral_constant<int, 256>{}, integral_constant<int, 1>{});
+    else if (n <= BATCH_MEDIUM) f(integral_constant<int, 1024>{}, integral_constant<int, 1>{});
+    else f(integral_constant<int, 1024>{}, integral_constant<int, 4>{});
+}
+
 hipError_t launch_emb_dedup(long long n, const uint64_t* ids, uint64_t* unique, int* occ, int* inverse,
                             long long* num_unique, void* ws, hipStream_t s) {
-    const size_t tcap = dedup_set_capacity(n);
-    const size_t nblk = (tcap + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    auto a = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    char* w = (char*)ws;
-    uint64_t* tkeys = (uint64_t*)w;
-    w += a(tcap * 8);
-    int* tocc = (int*)w;
-    w += a(tcap * 4);
-    int* rank = (int*)w;
-    w += a(tcap * 4);
-    int* pos = (int*)w;
-    w += a((size_t)n * 4);
-    int* bsum = (int*)w;
-    fill_u64_kernel<<<grid_for(tcap), THREADS, 0, s>>>(tkeys, (long long)tcap, KEY_EMPTY);
-    fill_i32_kernel<<<grid_for(tcap), THREADS, 0, s>>>(tocc, (long long)tcap, 0);
-    if (n > 0)
-        dedup_insert_kernel<<<(int)((n + DEDUP_CHUNK - 1) / DEDUP_CHUNK), THREADS, 0, s>>>(n, ids, tkeys, tocc, pos,
-                                                                                         (long long)tcap - 1);
-    scan_count_kernel<<<(int)nblk, THREADS, 0, s>>>(tkeys, (long long)tcap, bsum);
-    scan_top_kernel<<<1, THREADS, 0, s>>>(bsum, (long long)nblk, num_unique);
-    scan_emit_kernel<<<(int)nblk, THREADS, 0, s>>>(tkeys, tocc, (long long)tcap, bsum, rank, unique, occ);
-    if (n > 0) dedup_inverse_kernel<<<grid_for(n), THREADS, 0, s>>>(n, pos, rank, inverse);
+    const long long tcap = (long long)dedup_set_capacity(n);
+    SetEntry* set = (SetEntry*)ws;
+    int* pos = (int*)((char*)ws + align256(tcap * sizeof(SetEntry)));
+    int* uslot = (int*)((char*)pos + align256((size_t)n * 4));
+    dedup_clear_kernel<<<grid_for(tcap), THREADS, 0, s>>>(set, tcap, num_unique);
+    if (n > 0) {
+        by_batch(n, [&](auto tpb, auto per) {
+            constexpr int TPB = decltype(tpb)::value, PER = decltype(per)::value;
+            dedup_insert_kernel<TPB, PER><<<(int)((n + TPB * PER - 1) / (TPB * PER)), TPB, 0, s>>>(
+                n, ids, set, pos, tcap - 1, unique, uslot, num_unique);
+        });
+        dedup_finish_kernel<<<grid_for(n), THREADS, 0, s>>>(n, set, pos, uslot, num_unique, inverse, occ);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_emb_lookup(const EmbArgs& t, long long n_max, const uint64_t* unique, const int* occ,
-                             const long long* num_unique, int now, int insert, int* rows, void* ws,
-                             hipStream_t s) {
-    auto a = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    int* lpos = (int*)ws;
-    int* lfresh = (int*)((char*)ws + a((size_t)n_max * 4));
-    lookup_probe_kernel<<<grid_for(n_max), THREADS, 0, s>>>(t, n_max, unique, num_unique, insert, lpos, lfresh);
-    lookup_finish_kernel<<<grid_for(n_max), THREADS, 0, s>>>(t, n_max, occ, num_unique, now, lpos, lfresh, rows);
-    fixup_kernel<<<1, 1, 0, s>>>(t);
+                             const long long* num_unique, int now, int insert, int* rows, hipStream_t s) {
+    lookup_kernel<<<grid_for(n_max), THREADS, 0, s>>>(t, n_max, unique, occ, num_unique, now, insert, rows);
     return hipGetLastError();
-}
-
-size_t lookup_workspace_bytes(long long n_max) {
-    auto a = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    return 2 * a((size_t)n_max * 4);
 }
 
 hipError_t launch_emb_gather(const EmbArgs& t, long long n, const int* inverse, const int* rows, void* out,
@@ -691,63 +725,56 @@ hipError_t launch_emb_gather(const EmbArgs& t, long long n, const int* inverse, 
     return hipGetLastError();
 }
 
-namespace {
-struct SgdLayout {
-    size_t acc, start, cursor, list, lu, bsum, count, total;
-};
-SgdLayout sgd_layout(long long n, long long n_max, int dim) {
-    auto a = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const size_t nblk = ((size_t)n_max + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    SgdLayout L;
-    L.acc = 0;
-    L.start = L.acc + a((size_t)n_max * dim * sizeof(float));
-    L.cursor = L.start + a(((size_t)n_max + 1) * 4);
-    L.list = L.cursor + a((size_t)n_max * 4);
-    L.lu = L.list + a((size_t)n * 4);
-    L.bsum = L.lu + a((size_t)n * 4);
-    L.count = L.bsum + a((nblk + 1) * 4);
-    L.total = L.count + 256;
-    return L;
+// Workspace of the SGD step at `ws`, its size in *bytes.
+static SgdWork sgd_work(long long n, long long n_max, int dim, int esize, void* ws, size_t* bytes) {
+    const int cpb = sgd_chunks(dim, esize);
+    const long long places = (long long)cpb * sgd_chunk_len(cpb);
+    SgdWork w;
+    w.groups = (n + places - 1) / places;
+    char* p = (char*)ws;
+    auto take = [&](size_t b) {
+        char* r = p;
+        p += align256(b);
+        return r;
+    };
+    w.acc = (float*)take((size_t)w.groups * dim * sizeof(float));
+    w.span = (int*)take((size_t)w.groups * sizeof(int));
+    w.total = (int*)take(sizeof(int));
+    w.cursor = (int*)take((size_t)n_max * sizeof(int));
+    w.list = (int2*)take((size_t)n * sizeof(int2));
+    *bytes = (size_t)(p - (char*)ws);
+    return w;
 }
-}  // namespace
 
-size_t sgd_workspace_bytes(long long n, long long n_max, int dim) { return sgd_layout(n, n_max, dim).total; }
+// (the query does not know the table's dtype: the larger of both)
+size_t sgd_workspace_bytes(long long n, long long n_max, int dim) {
+    size_t b2, b4;
+    sgd_work(n, n_max, dim, 2, nullptr, &b2);
+    sgd_work(n, n_max, dim, 4, nullptr, &b4);
+    return max(b2, b4);
+}
 
 hipError_t launch_emb_sgd(const EmbArgs& t, long long n, const int* inverse, const int* occ, const void* grad,
                           long long ld_grad, long long n_max, const int* rows, const long long* num_unique,
                           float lr, void* ws, hipStream_t s) {
-    const SgdLayout L = sgd_layout(n, n_max, t.dim);
-    char* w = (char*)ws;
-    float* acc = (float*)(w + L.acc);
-    int* start = (int*)(w + L.start);
-    int* cursor = (int*)(w + L.cursor);
-    int* list = (int*)(w + L.list);
-    int* lu = (int*)(w + L.lu);
-    int* bsum = (int*)(w + L.bsum);
-    long long* count = (long long*)(w + L.count);
-    const long long nblk = (n_max + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    const long long cells = n_max * t.dim;
-    fill_f32_kernel<<<grid_for(cells), THREADS, 0, s>>>(acc, cells, 0.f);
-    if (n > 0) {
-        fill_i32_kernel<<<grid_for(n_max), THREADS, 0, s>>>(cursor, n_max, 0);
-        iscan_count_kernel<<<(int)nblk, THREADS, 0, s>>>(occ, num_unique, n_max, bsum);
-        scan_top_kernel<<<1, THREADS, 0, s>>>(bsum, nblk, count);
-        iscan_apply_kernel<<<(int)nblk, THREADS, 0, s>>>(occ, num_unique, n_max, bsum, start);
-        group_scatter_kernel<<<(int)((n + DEDUP_CHUNK - 1) / DEDUP_CHUNK), THREADS, 0, s>>>(n, inverse, start, cursor,
-                                                                                          list, lu);
-        const int cpr = t.dim * t.esize / 16, cpb = THREADS / cpr;
-        const long long nchunk = (n + GROUP_CHUNK - 1) / GROUP_CHUNK;
-        const int blocks = (int)((nchunk + cpb - 1) / cpb);
-        if (t.esize == 2)
-            group_sum_kernel<2><<<blocks, THREADS, 0, s>>>(t, n, list, lu, start, occ, grad, ld_grad, acc);
-        else
-            group_sum_kernel<4><<<blocks, THREADS, 0, s>>>(t, n, list, lu, start, occ, grad, ld_grad, acc);
+    if (n == 0) return hipSuccess;
+    size_t bytes;
+    const SgdWork w = sgd_work(n, n_max, t.dim, t.esize, ws, &bytes);
+    const int starts = START_PER * THREADS;
+    sgd_clear_kernel<<<grid_for(w.groups * t.dim), THREADS, 0, s>>>(w, t.dim);
+    sgd_start_kernel<<<(int)((n_max + starts - 1) / starts), THREADS, 0, s>>>(w, occ, num_unique, n_max);
+    by_batch(n, [&](auto tpb, auto per) {
+        constexpr int TPB = decltype(tpb)::value, PER = decltype(per)::value;
+        sgd_scatter_kernel<TPB, PER><<<(int)((n + TPB * PER - 1) / (TPB * PER)), TPB, 0, s>>>(w, n, inverse);
+    });
+    const int spans = grid_for(w.groups * (t.dim * t.esize / 16));
+    if (t.esize == 2) {
+        sgd_sum_kernel<2><<<(int)w.groups, THREADS, 0, s>>>(t, w, n, n_max, occ, rows, grad, ld_grad, lr);
+        sgd_span_kernel<2><<<spans, THREADS, 0, s>>>(t, w, rows, lr);
+    } else {
+        sgd_sum_kernel<4><<<(int)w.groups, THREADS, 0, s>>>(t, w, n, n_max, occ, rows, grad, ld_grad, lr);
+        sgd_span_kernel<4><<<spans, THREADS, 0, s>>>(t, w, rows, lr);
     }
-    const int epc = 16 / t.esize;
-    if (t.esize == 2)
-        sgd_apply_kernel<2><<<grid_for(n_max * (t.dim / epc)), THREADS, 0, s>>>(t, n_max, rows, num_unique, acc, lr);
-    else
-        sgd_apply_kernel<4><<<grid_for(n_max * (t.dim / epc)), THREADS, 0, s>>>(t, n_max, rows, num_unique, acc, lr);
     return hipGetLastError();
 }
 

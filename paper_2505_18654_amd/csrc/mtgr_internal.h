@@ -174,13 +174,11 @@ struct EmbArgs {
 };
 size_t dedup_set_capacity(long long n);
 size_t dedup_workspace_bytes(long long n);
-size_t lookup_workspace_bytes(long long n_max);
 hipError_t launch_emb_init(const EmbArgs& t, hipStream_t s);
 hipError_t launch_emb_dedup(long long n, const uint64_t* ids, uint64_t* unique, int* occ, int* inverse,
                             long long* num_unique, void* ws, hipStream_t s);
 hipError_t launch_emb_lookup(const EmbArgs& t, long long n_max, const uint64_t* unique, const int* occ,
-                             const long long* num_unique, int now, int insert, int* rows, void* ws,
-                             hipStream_t s);
+                             const long long* num_unique, int now, int insert, int* rows, hipStream_t s);
 hipError_t launch_emb_gather(const EmbArgs& t, long long n, const int* inverse, const int* rows, void* out,
                              long long ld_out, hipStream_t s);
 size_t sgd_workspace_bytes(long long n, long long n_max, int dim);
