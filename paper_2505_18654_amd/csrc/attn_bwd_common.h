@@ -24,22 +24,22 @@ __device__ __forceinline__ void zero(floatx16& x) {
 // and the copies are HIST_STRIDE = 65 words apart so that one bucket of different copies sits
 // in different banks.  8.3 KB.
 constexpr int HIST_COPIES = 32;
-constexpr int HIST_STRIDE = MTGR_RAB_LDS + 1;
+constexpr int HIST_STRIDE = RAB_SLOTS;
 constexpr int HIST_WORDS = HIST_COPIES * HIST_STRIDE;
 __device__ __forceinline__ void hist_zero(float* hist, int tid) {
     for (int i = tid; i < HIST_WORDS; i += 256) hist[i] = 0.f;
 }
-__device__ __forceinline__ void hist_add(float* hist, int lane, int bucket, float v) {
-    atomicAdd(&hist[(lane & (HIST_COPIES - 1)) * HIST_STRIDE + bucket], v);
+__device__ __forceinline__ void hist_add(float* hist, int lane, uint32_t index, float v) {
+    atomicAdd(&hist[(lane & (HIST_COPIES - 1)) * HIST_STRIDE + rab_slot(index)], v);
 }
 // Per-lane run of equal buckets: consecutive scores of a lane (queries of one key, or keys of
 // one query, in token order) mostly fall into the same log-time bucket, so each lane sums its
 // run in a register and touches the LDS histogram only when the bucket changes (and once at
 // the end).  LDS float atomics are slow on this chip; this makes them rare.
 struct HistRun {
-    int bucket = 0;
+    uint32_t bucket = 0;      // as rab_index
     float sum = 0.f;
-    __device__ __forceinline__ void add(float* hist, int lane, int b, float v) {
+    __device__ __forceinline__ void add(float* hist, int lane, uint32_t b, float v) {
         if (v != 0.f) {
             if (b != bucket) {
                 if (sum != 0.f) hist_add(hist, lane, bucket, sum);
@@ -54,10 +54,14 @@ struct HistRun {
         sum = 0.f;
     }
 };
-__device__ __forceinline__ float hist_total(const float* hist, int bucket) {
+// Sum of bucket `bucket` over the copies (the last bucket: of every slot from its own on).
+__device__ __forceinline__ float hist_total(const float* hist, int bucket, int nb) {
+    const int first = bucket < 2 ? bucket : bucket + 1, last = bucket == nb - 1 ? RAB_SLOTS - 1 : first;
     float s = 0.f;
+    for (int x = first; x <= last; x++) {
 #pragma unroll 8
-    for (int c = 0; c < HIST_COPIES; c++) s += hist[c * HIST_STRIDE + bucket];
+        for (int c = 0; c < HIST_COPIES; c++) s += hist[c * HIST_STRIDE + x];
+    }
     return s;
 }
 }  // namespace bwd

@@ -17,7 +17,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     __shared__ __align__(16) uint16_t sV1[TILE];
     __shared__ int sKts[2][BN];
     __shared__ int sKcode[2][BN];
-    __shared__ float sRab[MTGR_RAB_LDS];
+    __shared__ float sRab[RAB ? RAB_TABLE : 1];
     __shared__ float sHist[RAB ? bwd::HIST_WORDS : 1];
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
         doreg[kk] = as_bf16x8(g);
     }
     if (RAB) {
-        if (tid < MTGR_RAB_LDS) sRab[tid] = tid < a.nbuckets ? NEG_LOG2E * a.rab[h * a.nbuckets + tid] : 0.f;
+        rab_fill(sRab, a.rab + h * a.nbuckets, a.nbuckets, NEG_LOG2E, tid);
         bwd::hist_zero(sHist, tid);
     }
     floatx16 dqacc[DBLK];
@@ -114,12 +114,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
 #pragma unroll
             for (int g0 = 0; g0 < 16; g0 += GRP) {
                 float dv[GRP];
-                int bk[GRP];
+                uint32_t bk[GRP];
                 if (RAB) {
 #pragma unroll
                     for (int e = 0; e < GRP; e++) {
                         const int rr = g0 + e;
-                        bk[e] = rab_bucket(qts, kts[32 * blk + 8 * (rr >> 2) + 4 * hh + (rr & 3)], a.nbuckets);
+                        bk[e] = rab_index(ts_key(qts), ts_key(kts[32 * blk + 8 * (rr >> 2) + 4 * hh + (rr & 3)]));
                     }
                 }
 #pragma unroll
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
         run.flush(sHist, lane);
         __syncthreads();   // zeroing (when no tile was visited) and every histogram update
         if (tid < a.nbuckets) {
-            const float v = bwd::hist_total(sHist, tid);
+            const float v = bwd::hist_total(sHist, tid, a.nbuckets);
             if (v != 0.f) atomicAdd(&a.drab[h * a.nbuckets + tid], v * inv_n);
         }
     }

@@ -74,10 +74,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
 
     __shared__ __align__(16) uint16_t sK[2][TILE];
     __shared__ __align__(16) uint16_t sV[2][TILE];
-    __shared__ int sVts[2][BN];          // timestamps / mask codes travel with the V tile
+    __shared__ int sVts[2][BN];          // timestamps (with a bias: ts_key) / mask codes travel with the V tile
     __shared__ int sVcode[2][BN];
     __shared__ __align__(16) long long sVthr[2][BN];   // key_threshold of each key of the tile
-    __shared__ float sRab[MTGR_RAB_LDS];
+    __shared__ float sRab[RAB ? RAB_TABLE : 1];
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int2 item = a.items[blockIdx.x];
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     const int* kcode_g = (CACHED ? a.tok_code_k : a.tok_code) + okb;
     const uint16_t* Qb = (const uint16_t*)a.q + (long long)ob * a.ld_q;
     bf16x8 qreg[KSTEPS];
-    if (RAB && tid < MTGR_RAB_LDS) sRab[tid] = tid < a.nbuckets ? NEG_LOG2E * a.rab[h * a.nbuckets + tid] : 0.f;
+    if (RAB) rab_fill(sRab, a.rab + h * a.nbuckets, a.nbuckets, NEG_LOG2E, tid);
 
     // Per-lane LDS byte offsets of the MFMA operands, shared by every tile and buffer: the
     // K operand of k-step kk (row col, chunk 2 kk + hh; rows 32..63 add 32 * CPR * 16 bytes)
@@ -154,6 +154,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     // -log2(e) silu(alpha s + rab) = y / (1 + 2^y), y = -log2(e) (alpha s + rab) (the table in LDS
     // holds -log2(e) rab).
     const float c_exp = -1.4426950408889634f * alpha;
+    const uint32_t qkey = ts_key(qts);
     // qrel = qi - (first key of the tile) - 4 hh; the key of element e of half HC is the
     // tile's key 32 HC + 8 (e / 4) + 4 hh + e % 4, so the diagonal test compares qrel with a
     // compile-time constant.
@@ -162,11 +163,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
         float p;
         if (RAB) {
             float sg;
-            p = silu_scaled(__builtin_fmaf(sv, c_exp, sRab[rab_bucket(qts, kts[kl], a.nbuckets)]), sg);
+            p = silu_scaled(__builtin_fmaf(sv, c_exp, sRab[rab_index(qkey, (uint32_t)kts[kl])]), sg);
         } else {
             p = sv * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(sv * c_exp));
         }
-        if (MASKED) p = visible_diag(qcode, qts, kcode[kl], kts[kl], qrel == kc) ? p : 0.f;
+        if (MASKED) p = visible_diag(qcode, qkey, kcode[kl], (uint32_t)kts[kl], qrel == kc) ? p : 0.f;
         return p;
     };
 
@@ -332,7 +333,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
                 // padded keys get code 0; every key gets its visibility threshold
                 int c = sVcode[P][tid];
                 if (t0 * BN + tid >= nkb) sVcode[P][tid] = c = 0;
-                sVthr[P][tid] = key_threshold(c, sVts[P][tid]);
+                const int kt = sVts[P][tid];
+                sVthr[P][tid] = key_threshold(c, kt);
+                if (RAB) sVts[P][tid] = (int)ts_key(kt);
             }
             lds_barrier();
             if (t1 < ntk) issue_v(t1, P ^ 1);                      // V(t_{i-1})'s buffer

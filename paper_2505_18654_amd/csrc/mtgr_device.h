@@ -148,8 +148,10 @@ __device__ __forceinline__ long long query_value(int qcode, int qts) {
     return (qcode & KC_DYN) ? (long long)qts : (long long)0x8000000000000000ull;
 }
 
-// visible() with the diagonal test i == j already evaluated by the caller.
-__device__ __forceinline__ bool visible_diag(int qcode, int qts, int kcode, int kts, bool diag) {
+// visible() with the diagonal test i == j already evaluated by the caller (TS: int timestamps or
+// their ts_key).
+template <class TS>
+__device__ __forceinline__ bool visible_diag(int qcode, TS qts, int kcode, TS kts, bool diag) {
     const int both_valid = kcode & qcode & KC_VALID;
     const int rule2 = (kcode & KC_RT) & ((qcode & KC_DYN) >> 1) & (kts < qts ? KC_RT : 0);
     const int seen = (kcode & KC_STATIC) | (diag ? 1 : 0) | (rule2 >> 1);
@@ -167,6 +169,32 @@ __device__ __forceinline__ int rab_bucket(int a, int b, int nb) {
         bk = 2 * e + (int)((g >> (e - 1)) & 1u);
     }
     return min(bk, nb - 1);
+}
+
+// The same bucket in the bf16 kernels' inner loops, in six operations instead of about fourteen.
+// Timestamps are kept as ts_key (int32 order as uint32), whose distance is one v_sad_u32; converting
+// the gap to float puts floor(log2 gap) and the next bit on top of the word, so that its leading
+// ten bits count half octaves:
+//   gap 0: 0, gap 1: 254, gap g >= 2: 254 + 2 floor(log2 g) + [g >= 1.5 2^floor(log2 g)].
+// The conversion rounds gaps of 2^24 and more; clearing the bits under (gap >> 2) first clears the
+// third bit from the top (and keeps the two above it), which no carry passes.  The LDS table is
+// indexed by that number directly (RAB_TABLE entries, each bucket's value with the clamp to the
+// last one applied), and the drab histogram by rab_slot, which packs the 65 numbers in use.
+// Measured (128 users, 74 k tokens, 4 heads of 128, 64 buckets): forward 241 -> 221 us, dK/dV
+// 515 -> 499 us (with its mask by ts_key), dQ recomputing S and dP 306 -> 275 us.
+constexpr int RAB_TABLE = 318, RAB_SLOTS = 65;
+__device__ __forceinline__ uint32_t ts_key(int ts) { return (uint32_t)ts ^ 0x80000000u; }
+__device__ __forceinline__ uint32_t rab_index(uint32_t a, uint32_t b) {
+    uint32_t g;
+    asm("v_sad_u32 %0, %1, %2, 0" : "=v"(g) : "v"(a), "v"(b));
+    return __float_as_uint((float)(g & ~(g >> 2))) >> 22;
+}
+// slot 0: gap 0; 1: gap 1; 3 .. 64: buckets 2 .. 63
+__device__ __forceinline__ uint32_t rab_slot(uint32_t index) { return max(index, 253u) - 253u; }
+__device__ __forceinline__ int rab_slot_bucket(int slot, int nb) { return min(slot < 2 ? slot : slot - 1, nb - 1); }
+// Fills the table (every thread of the 256) with scale times the head's bias row.
+__device__ __forceinline__ void rab_fill(float* table, const float* rab, int nb, float scale, int tid) {
+    for (int i = tid; i < RAB_TABLE; i += 256) table[i] = scale * rab[rab_slot_bucket((int)rab_slot(i), nb)];
 }
 
 // With a relative bias the forward and the recomputing dQ kernel keep the bias table in LDS
