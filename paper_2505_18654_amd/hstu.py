@@ -158,17 +158,29 @@ def _check(status: int) -> None:
 
 def _ptr(x) -> Optional[int]:
     """Device (or host) address of a tensor, an int address, or None."""
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
     return x.data_ptr()
 
 
+_raw_stream = None
+
+
+def _current_stream() -> int:
+    """The handle of torch's current stream on the current device.  Asked for once per call, so it
+    goes past the Stream object that torch.cuda.current_stream() builds (2.7 of a call's 12 us)."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()                      # initialises CUDA, or says why it cannot
+        raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        _raw_stream = lambda: raw(device())              # noqa: E731
+    return _raw_stream()
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -38,8 +38,8 @@ class LayerParams:
 
 def _split(a: torch.Tensor, d: int, heads: int):
     T = a.shape[0]
-    cols = [a[:, i * d:(i + 1) * d] for i in range(4)]
-    return [c.view(T, heads, d // heads) for c in cols[:3]] + [cols[3]]
+    q, k, v, _ = a.view(T, 4, heads, d // heads).unbind(1)
+    return q, k, v, a[:, 3 * d:]
 
 
 def layer_fwd(x: torch.Tensor, jag: ops.Jagged, P: LayerParams, heads: int, rab=None, alpha: float = 1.0,

@@ -24,15 +24,16 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 def _token_stride(t: torch.Tensor, inner: int) -> int:
     """Token stride of a [T, H, dh] or [T, d] view whose inner dims are dense."""
-    if t.dim() == 3:
-        if t.stride(2) != 1 or t.stride(1) != t.shape[2]:
+    st, sh = t.stride(), t.shape
+    if len(st) == 3:
+        if st[2] != 1 or st[1] != sh[2]:
             raise ValueError("head and feature dims must be dense")
-    elif t.dim() == 2:
-        if t.stride(1) != 1:
+    elif len(st) == 2:
+        if st[1] != 1:
             raise ValueError("feature dim must be dense")
-    if t.shape[0] <= 1:
+    if sh[0] <= 1:
         return inner
-    return t.stride(0)
+    return st[0]
 
 
 def _like_layout(t: torch.Tensor) -> torch.Tensor:
@@ -71,9 +72,13 @@ def attn_problem(jag: Jagged, q, k, v, out, rab=None, alpha: float = 1.0,
     T, H, dh = q.shape
     row = H * dh
     nb = 0 if rab is None else rab.shape[1]
-    return hstu.attn_problem(jag.num_users, T, jag.max_seqlen, H, dh, _dtype_code(q), alpha, nb,
-                             _token_stride(q, row), _token_stride(k, row), _token_stride(v, row),
-                             _token_stride(out, row), flags)
+    # (a tensor given for several arguments, as by attn_plan, has one stride)
+    lq = _token_stride(q, row)
+    lk = lq if k is q else _token_stride(k, row)
+    lv = lk if v is k else _token_stride(v, row)
+    lo = lq if out is q else _token_stride(out, row)
+    return hstu.HstuProblem(jag.num_users, jag.max_seqlen, T, H, dh, _dtype_code(q), alpha, nb, flags,
+                            lq or row, lk or row, lv or row, lo or row)
 
 
 def validate_batch(jag: Jagged, group_ids=None, num_groups: int = 0, scratch=None) -> None:
@@ -169,9 +174,8 @@ def attn_bwd(q, k, v, dout, jag: Jagged, rab=None, alpha: float = 1.0, need_drab
         if not need_drab:
             drab = None
     p = attn_problem(jag, q, k, v, dout, rab, alpha, flags)
-    if _token_stride(dq, q.shape[1] * q.shape[2]) != p.ld_q or \
-            _token_stride(dk, q.shape[1] * q.shape[2]) != p.ld_k or \
-            _token_stride(dv, q.shape[1] * q.shape[2]) != p.ld_v:
+    row = q.shape[1] * q.shape[2]
+    if _token_stride(dq, row) != p.ld_q or _token_stride(dk, row) != p.ld_k or _token_stride(dv, row) != p.ld_v:
         raise ValueError("gradients must share the layout of q, k, v")
     if workspace is None:
         workspace = workspace_for(p, q.device, backward=True)
