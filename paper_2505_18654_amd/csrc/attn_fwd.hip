@@ -59,8 +59,16 @@ __device__ __forceinline__ uint4 ldg16(const uint16_t* p) { return *(const uint4
 // the sigmoid 0 and P'' = y * 0 (the host requires |alpha| >= 1e-7 and finite bias values
 // far below 1e29 for it).  RSEL instead selects P' = 0 element by element in the epilogue (a
 // second epilogue path): the host picks it for a bias with |alpha| < 1e-7.
-template <int DH, bool RAB, bool CACHED, bool RSEL>
-__global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
+//
+// Splitting the keys (G = 2).  With few (user, head, query tile) items the chip idles and the longest
+// user sets the time.  A workgroup then has two groups of 4 waves, one workgroup per CU, that take
+// the item's visible key tiles in turn, each with its own LDS buffers, and the second group's O
+// is added to the first's through LDS at the end.  Both go through the same number of tiles (and
+// barriers): when it is odd, the second group ends with a tile whose keys are all hidden.
+// Measured (serving users, 6 heads of 128): candidates of 8 users 65 -> 50 us, cached requests of
+// 1 / 4 / 8 users 21 -> 20, 33 -> 29 and 58 -> 49 us; one user of 3,000 tokens, 8 heads 40 -> 32 us.
+template <int DH, bool RAB, bool CACHED, bool RSEL, int G>
+__global__ __launch_bounds__(256 * G, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     constexpr int CPR = DH / 8;          // 16-byte chunks per row
     constexpr int KSTEPS = DH / 16;      // k-steps of S^T = K Q^T per 32-key half
     constexpr int DBLK = DH / 32;        // 32-row blocks of O^T (MFMAs per 16-key PV step)
@@ -72,14 +80,19 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     constexpr int PF = MTGR_FWD_PF;      // operand prefetch distance in MFMA slots
     constexpr int SB = MTGR_FWD_SB;      // MFMA slots per scheduling region
 
-    __shared__ __align__(16) uint16_t sK[2][TILE];
-    __shared__ __align__(16) uint16_t sV[2][TILE];
-    __shared__ int sVts[2][BN];          // timestamps (with a bias: ts_key) / mask codes travel with the V tile
-    __shared__ int sVcode[2][BN];
-    __shared__ __align__(16) long long sVthr[2][BN];   // key_threshold of each key of the tile
+    // per group: K buffers 0 and 1, V buffers 0 and 1
+    __shared__ __align__(16) uint16_t sKV[G][4][TILE];
+    __shared__ int sVtsG[G][2][BN];          // timestamps (with a bias: ts_key) / mask codes travel with the V tile
+    __shared__ int sVcodeG[G][2][BN];
+    __shared__ __align__(16) long long sVthrG[G][2][BN];   // key_threshold of each key of the tile
     __shared__ float sRab[RAB ? RAB_TABLE : 1];
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x & 255, lane = tid & 63, w = tid >> 6;     // within the group
+    const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    constexpr uint32_t GBYTES = 4 * TILE * 2;
+    uint16_t (*sK)[TILE] = sKV[grp], (*sV)[TILE] = sKV[grp] + 2;
+    int (*sVts)[BN] = sVtsG[grp], (*sVcode)[BN] = sVcodeG[grp];
+    long long (*sVthr)[BN] = sVthrG[grp];
     const int2 item = a.items[blockIdx.x];
     if (item.x < 0) return;
     const int b = item.x, qt = item.y >> 8, h = item.y & 255;
@@ -127,6 +140,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     // XOR 64 db: three live registers instead of KSTEPS + 2 DBLK.
     uint32_t kofs0 = tile_ofs<CPR>(col, hh), vofs0 = 0, vofs1 = 0;
     tile_ofs_tr<CPR>(0, lane, vofs0, vofs1);
+    // (offsets from group 0's tiles, so that the buffers stay compile-time constants)
+    kofs0 += grp * GBYTES;
+    vofs0 += grp * GBYTES;
+    vofs1 += grp * GBYTES;
     constexpr uint32_t ROW16 = 16u * CPR * 16u;   // bytes of 16 tile rows
 
     floatx16 oacc[DBLK];
@@ -191,8 +208,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
         constexpr bool HAS_NEXT = decltype(next_tag)::value;
         constexpr int VB = decltype(vb_tag)::value, HC = decltype(hc_tag)::value;
         constexpr int KB = decltype(kb_tag)::value, HN = decltype(hn_tag)::value;
-        const uint16_t* Vc = sV[VB];
-        const uint16_t* Kn = sK[KB];
+        const uint16_t* Vc = sKV[0][2 + VB];
+        const uint16_t* Kn = sKV[0][KB];
         // The XOR-derived operand offsets are loop invariants that the compiler keeps in registers
         // (16 reads' worth for 3 more VGPRs: 64 VALU instructions fewer per two tiles).  The
         // select-masked bias instantiation, at 256 VGPRs, derives them afresh in every half-step
@@ -289,9 +306,21 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     using T = std::true_type;
     using F = std::false_type;
 
-    int cls0, cls1 = TILE_MASKED;
-    int t0 = walk.next(0, &cls0);                                // t_i
-    int t1 = t0 < ntk ? walk.next(t0 + 1, &cls1) : ntk;          // t_{i+1}
+    // This group's next tile after tile t - 1, which the other group's next one precedes (group 1)
+    // or follows (group 0); *cls TILE_MASKED: the hidden last tile of group 1.
+    auto next_of = [&](int t, int* cls) {
+        if constexpr (G == 1) return walk.next(t, cls);
+        int c;
+        const int other = walk.next(t, &c);
+        if (other >= ntk) return ntk;
+        const int mine = walk.next(other + 1, cls);
+        if (mine < ntk || grp == 0) return mine;
+        *cls = TILE_MASKED;
+        return other;
+    };
+    int cls0 = TILE_MASKED, cls1 = TILE_MASKED;
+    int t0 = grp == 0 ? walk.next(0, &cls0) : next_of(0, &cls0);     // t_i
+    int t1 = t0 < ntk ? next_of(t0 + 1, &cls1) : ntk;            // t_{i+1}
     // The workgroup's 128 query rows come in as two tiles, through the buffers of K(t_{i+1}) and
     // V(t_{i+1}) (copied later): whole rows per copy instruction, where per-lane loads of each
     // lane's operand chunks touched 32 rows per instruction (the forward took 12 % longer).
@@ -319,7 +348,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
         floatx16 sA, sB;                                         // S(t_i, keys 0..31) in sA
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; kk++)
-            sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read16(sK[0], kofs0 ^ (32u * kk)), qreg[kk],
+            sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read16(sKV[0][0], kofs0 ^ (32u * kk)), qreg[kk],
                                                         kk == 0 ? floatx16{} : sA, 0, 0, 0);
         // Tile t_i, whose K and V sit in buffers P (the tile loop is unrolled by two so that P
         // is a compile-time constant).  Returns false after the last tile.
@@ -332,16 +361,16 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
             if (tid < BN) {
                 // padded keys get code 0; every key gets its visibility threshold
                 int c = sVcode[P][tid];
-                if (t0 * BN + tid >= nkb) sVcode[P][tid] = c = 0;
+                if (t0 * BN + tid >= nkb || (G > 1 && cls0 == TILE_MASKED)) sVcode[P][tid] = c = 0;
                 const int kt = sVts[P][tid];
                 sVthr[P][tid] = key_threshold(c, kt);
                 if (RAB) sVts[P][tid] = (int)ts_key(kt);
             }
             lds_barrier();
             if (t1 < ntk) issue_v(t1, P ^ 1);                      // V(t_{i-1})'s buffer
-            const bool partial = cls0 == TILE_PARTIAL;
-            // (cached: no key is the query itself, so the diagonal test never holds)
-            const int qrel = CACHED ? -(1 << 20) : qi - t0 * BN - 4 * hh;
+            const bool partial = cls0 != TILE_FULL;
+            // (cached, hidden tile: no key is the query itself, so the diagonal test never holds)
+            const int qrel = CACHED || (G > 1 && cls0 == TILE_MASKED) ? -(1 << 20) : qi - t0 * BN - 4 * hh;
             uint32_t pkA[4], pkB[4];
             // half 0 of t_i; next S = half 1 of t_i (same K buffer)
             if (SMASK && partial) premask(sA, C0{}, sVthr[P], qrel);
@@ -355,7 +384,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
                 // middle: K(t_{i+1}) landed everywhere and K(t_i) is no longer read -> K(t_{i+2})
                 if (w == 0) wait_vmcnt<NK + 2>(); else wait_vmcnt<NK>();
                 lds_barrier();
-                t2 = walk.next(t1 + 1, &cls2);
+                t2 = next_of(t1 + 1, &cls2);
                 if (t2 < ntk) issue_k(t2, P);
             }
             // half 1 of t_i; next S = half 0 of t_{i+1}.  After the last tile that S is formed
@@ -371,7 +400,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
 #pragma unroll
             for (int db = 0; db < DBLK; db++)
                 oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    lds_read_tr(sV[P], (vofs0 ^ (64u * db)) + 3 * ROW16, (vofs1 ^ (64u * db)) + 3 * ROW16), pb,
+                    lds_read_tr(sKV[0][2 + P], (vofs0 ^ (64u * db)) + 3 * ROW16, (vofs1 ^ (64u * db)) + 3 * ROW16), pb,
                     oacc[db], 0, 0, 0);
             const bool more = t1 < ntk;
             t0 = t1;
@@ -383,6 +412,31 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
         while (tile(C0{}) && tile(C1{})) {
         }
         __syncthreads();                                         // K buffers are reused below
+    }
+    if constexpr (G > 1) {
+        // group 1's O through its own K and V buffers, 16 bytes per lane and write
+        float4* part = (float4*)sKV[1][0];
+        static_assert(DBLK * 4 * 256 * 16 <= GBYTES, "O fits a group's buffers");
+        if (grp == 1) {
+#pragma unroll
+            for (int db = 0; db < DBLK; db++)
+#pragma unroll
+                for (int g = 0; g < 4; g++)
+                    part[(4 * db + g) * 256 + tid] = make_float4(oacc[db][4 * g], oacc[db][4 * g + 1],
+                                                                 oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
+        }
+        __syncthreads();
+        if (grp == 1) return;
+#pragma unroll
+        for (int db = 0; db < DBLK; db++)
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const float4 p = part[(4 * db + g) * 256 + tid];
+                oacc[db][4 * g] += p.x;
+                oacc[db][4 * g + 1] += p.y;
+                oacc[db][4 * g + 2] += p.z;
+                oacc[db][4 * g + 3] += p.w;
+            }
     }
 
     if constexpr (CACHED) {
@@ -443,7 +497,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
                            pack_bf16x2(oacc[db][4 * g + 2] * oscale, oacc[db][4 * g + 3] * oscale));
         }
     }
-    __syncthreads();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (each wave reads only the rows it staged)
     uint16_t* O = (uint16_t*)a.out;
 #pragma unroll
     for (int i = 0; i < 32 * CPR / 64; i++) {
@@ -538,15 +592,26 @@ __global__ __launch_bounds__(256) void attn_fwd_vec_kernel(AttnArgs a) {
     }
 }
 
+template <int DH, bool CACHED, int G>
+static hipError_t fwd_bf16_groups(const AttnArgs& a, int slots, hipStream_t s) {
+    if (a.rab && fabsf(a.alpha) >= 1e-7f)
+        attn_fwd_bf16_kernel<DH, true, CACHED, false, G><<<slots, 256 * G, 0, s>>>(a);
+    else if (a.rab)
+        attn_fwd_bf16_kernel<DH, true, CACHED, true, 1><<<slots, 256, 0, s>>>(a);
+    else
+        attn_fwd_bf16_kernel<DH, false, CACHED, false, G><<<slots, 256 * G, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+// Two groups per workgroup pay while every item has a CU to itself, so up to about 256 items; the
+// host knows the work list's slots, an upper bound.  Forwards of 72 to 328 slots took 0.77 to 0.97
+// of their time with one group, 376 slots (32 users of 180 tokens) 1.09, 536 to 872 (24 to 32
+// serving users) 1.2 to 1.36.
+constexpr int SPLIT_SLOTS = 320;
+
 template <int DH, bool CACHED>
 static hipError_t fwd_bf16_dh(const AttnArgs& a, int slots, hipStream_t s) {
-    if (a.rab && fabsf(a.alpha) >= 1e-7f)
-        attn_fwd_bf16_kernel<DH, true, CACHED, false><<<slots, 256, 0, s>>>(a);
-    else if (a.rab)
-        attn_fwd_bf16_kernel<DH, true, CACHED, true><<<slots, 256, 0, s>>>(a);
-    else
-        attn_fwd_bf16_kernel<DH, false, CACHED, false><<<slots, 256, 0, s>>>(a);
-    return hipGetLastError();
+    return slots <= SPLIT_SLOTS ? fwd_bf16_groups<DH, CACHED, 2>(a, slots, s) : fwd_bf16_groups<DH, CACHED, 1>(a, slots, s);
 }
 
 template <int DH, class E>
