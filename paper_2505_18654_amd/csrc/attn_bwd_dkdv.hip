@@ -347,10 +347,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) 
     if (want_drab) {
         run.flush(sHist, lane);
         __syncthreads();   // every wave's histogram updates have landed
-        if (tid < a.nbuckets) {
-            const float v = bwd::hist_total(sHist, tid, a.nbuckets);
-            if (v != 0.f) atomicAdd(&a.drab[h * a.nbuckets + tid], v * inv_n);
-        }
+        bwd::hist_finish(sHist, a.nbuckets, inv_n, a.drab + h * a.nbuckets, tid);
     }
     // dK^T / dV^T accumulators: lane = key row, registers = features, so that a lane packs four
     // consecutive features per LDS write (as dK / dV, lane = feature, each value was a 2-byte

@@ -178,10 +178,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     if (want_drab) {
         run.flush(sHist, lane);
         __syncthreads();   // zeroing (when no tile was visited) and every histogram update
-        if (tid < a.nbuckets) {
-            const float v = bwd::hist_total(sHist, tid, a.nbuckets);
-            if (v != 0.f) atomicAdd(&a.drab[h * a.nbuckets + tid], v * inv_n);
-        }
+        bwd::hist_finish(sHist, a.nbuckets, inv_n, a.drab + h * a.nbuckets, tid);
     }
     uint16_t* sO = (w < 2 ? sK0 : sK1) + (w & 1) * 32 * DH;
     const float dq_scale = alpha * inv_n;
