@@ -35,12 +35,17 @@ using bwd::BN;
 
 // ------------------------------------------------------------------ vector-ALU kernels
 // fp32 storage (the parity mode) or bf16 storage at head_dim 16 (see the forward's vector
-// kernel); arithmetic in fp32.  dq kernel: 64 query rows, 4 threads per row (dh/4 features each); keys staged 32 at a time.
+// kernel, also for the quad's four keys at a time); arithmetic in fp32.  dq kernel: 64 query rows, 4
+// threads per row (dh/4 features each); keys staged 64 (32 at dh 128) at a time.  At dh 64 and 128
+// the four rows of a step are read from LDS again for the second product: kept in registers they
+// left room for one wave per SIMD (dq at dh 128, 64 users: 788 us one key at a time, 747 us kept,
+// 322 us read again; the dkdv kernel, with four accumulator rows, is faster keeping them: 654, 524
+// and 704 us).
 template <int DH, bool RAB, class E>
 __global__ __launch_bounds__(256) void attn_bwd_dq_vec_kernel(AttnArgs a) {
-    constexpr int BMF = 64, SUB = 32, Q4 = DH / 4, KP = DH + 1;
-    __shared__ float sK[SUB * KP];
-    __shared__ float sV[SUB * KP];
+    constexpr int BMF = 64, SUB = DH <= 64 ? 64 : 32, Q4 = DH / 4;
+    __shared__ __align__(16) float sK[SUB * DH];
+    __shared__ __align__(16) float sV[SUB * DH];
     __shared__ int sKcode[SUB];
     __shared__ int sKts[SUB];
     __shared__ float sRab[MTGR_RAB_LDS];
@@ -86,8 +91,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_vec_kernel(AttnArgs a) {
             __syncthreads();
             for (int i = tid; i < SUB * DH; i += 256) {
                 const int row = i / DH, c = i % DH, key = kb + row;
-                sK[row * KP + c] = key < nb ? ld_elem(K, (long long)(ob + key) * a.ld_k + h * DH + c) : 0.f;
-                sV[row * KP + c] = key < nb ? ld_elem(V, (long long)(ob + key) * a.ld_v + h * DH + c) : 0.f;
+                sK[i] = key < nb ? ld_elem(K, (long long)(ob + key) * a.ld_k + h * DH + c) : 0.f;
+                sV[i] = key < nb ? ld_elem(V, (long long)(ob + key) * a.ld_v + h * DH + c) : 0.f;
             }
             if (tid < SUB) {
                 const int key = kb + tid;
@@ -95,30 +100,40 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_vec_kernel(AttnArgs a) {
                 sKts[tid] = key < nb ? a.ts[ob + key] : 0;
             }
             __syncthreads();
-            for (int j = 0; j < SUB; j++) {
-                float s = 0.f, dp = 0.f;
+#pragma unroll (DH <= 32 ? 2 : 1)
+            for (int j = 0; j < SUB; j += 4) {
+                float s4[4], d4[4];
 #pragma unroll
-                for (int c = 0; c < Q4; c++) {
-                    s = fmaf(qv[c], sK[j * KP + part * Q4 + c], s);
-                    dp = fmaf(gv[c], sV[j * KP + part * Q4 + c], dp);
+                for (int k = 0; k < 4; k++) {
+                    s4[k] = d4[k] = 0.f;
+#pragma unroll
+                    for (int c = 0; c < Q4; c++) {
+                        s4[k] = fmaf(qv[c], sK[(j + k) * DH + part * Q4 + c], s4[k]);
+                        d4[k] = fmaf(gv[c], sV[(j + k) * DH + part * Q4 + c], d4[k]);
+                    }
                 }
-                s += __shfl_xor(s, 1, 64);
-                s += __shfl_xor(s, 2, 64);
-                dp += __shfl_xor(dp, 1, 64);
-                dp += __shfl_xor(dp, 2, 64);
-                float x = s * a.alpha;
+                const int jk = j + part;                       // this thread's key of the four
+                const float dp = quad_sum4(d4, part);
+                float x = quad_sum4(s4, part) * a.alpha;
                 int bk = 0;
                 if (RAB) {
-                    bk = rab_bucket(qts, sKts[j], a.nbuckets);
+                    bk = rab_bucket(qts, sKts[jk], a.nbuckets);
                     x += sRab[bk];
                 }
                 const float sg = 1.0f / (1.0f + expf(-x));
                 const float ds = dp * sg * (1.0f + x * (1.0f - sg)) * inv_n;
-                if (visible(qcode, qts, qi, sKcode[j], sKts[j], kb + j)) {
+                const int vis = visible(qcode, qts, qi, sKcode[jk], sKts[jk], kb + jk) ? 1 : 0;
+                if (want_drab && vis) atomicAdd(&sHist[bk], ds);
+                const float dk[4] = {quad_lane<0>(ds), quad_lane<1>(ds), quad_lane<2>(ds), quad_lane<3>(ds)};
+                const int vk[4] = {quad_lane<0>(vis), quad_lane<1>(vis), quad_lane<2>(vis), quad_lane<3>(vis)};
+                if constexpr (DH >= 64) asm volatile("" ::: "memory");   // read the rows again (see above)
 #pragma unroll
-                    for (int c = 0; c < Q4; c++) acc[c] = fmaf(ds, sK[j * KP + part * Q4 + c], acc[c]);
-                    if (want_drab && part == 0) atomicAdd(&sHist[bk], ds);
-                }
+                for (int k = 0; k < 4; k++)
+#pragma unroll
+                    for (int c = 0; c < Q4; c++) {
+                        const float o = fmaf(dk[k], sK[(j + k) * DH + part * Q4 + c], acc[c]);
+                        acc[c] = vk[k] ? o : acc[c];
+                    }
             }
         }
     }
@@ -135,9 +150,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_vec_kernel(AttnArgs a) {
 // dkdv kernel: 64 key rows, 4 threads per key; queries staged 32 at a time.
 template <int DH, bool RAB, class E>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_vec_kernel(AttnArgs a) {
-    constexpr int BMF = 64, SUB = 32, Q4 = DH / 4, KP = DH + 1;
-    __shared__ float sQ[SUB * KP];
-    __shared__ float sG[SUB * KP];
+    constexpr int BMF = 64, SUB = DH <= 64 ? 64 : 32, Q4 = DH / 4;
+    __shared__ __align__(16) float sQ[SUB * DH];
+    __shared__ __align__(16) float sG[SUB * DH];
     __shared__ int sQcode[SUB];
     __shared__ int sQts[SUB];
     __shared__ float sRab[MTGR_RAB_LDS];
@@ -179,8 +194,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_vec_kernel(AttnArgs a) {
             __syncthreads();
             for (int i = tid; i < SUB * DH; i += 256) {
                 const int row = i / DH, c = i % DH, qr = qb + row;
-                sQ[row * KP + c] = qr < nb ? ld_elem(Q, (long long)(ob + qr) * a.ld_q + h * DH + c) : 0.f;
-                sG[row * KP + c] = qr < nb ? ld_elem(DO, (long long)(ob + qr) * a.ld_o + h * DH + c) : 0.f;
+                sQ[i] = qr < nb ? ld_elem(Q, (long long)(ob + qr) * a.ld_q + h * DH + c) : 0.f;
+                sG[i] = qr < nb ? ld_elem(DO, (long long)(ob + qr) * a.ld_o + h * DH + c) : 0.f;
             }
             if (tid < SUB) {
                 const int qr = qb + tid;
@@ -188,29 +203,38 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_vec_kernel(AttnArgs a) {
                 sQts[tid] = qr < nb ? a.ts[ob + qr] : 0;
             }
             __syncthreads();
-            for (int i = 0; i < SUB; i++) {
-                float s = 0.f, dp = 0.f;
+#pragma unroll (DH <= 32 ? 2 : 1)
+            for (int i = 0; i < SUB; i += 4) {
+                float s4[4], d4[4];
 #pragma unroll
-                for (int c = 0; c < Q4; c++) {
-                    s = fmaf(sQ[i * KP + part * Q4 + c], kv[c], s);
-                    dp = fmaf(sG[i * KP + part * Q4 + c], vv[c], dp);
+                for (int k = 0; k < 4; k++) {
+                    s4[k] = d4[k] = 0.f;
+#pragma unroll
+                    for (int c = 0; c < Q4; c++) {
+                        s4[k] = fmaf(sQ[(i + k) * DH + part * Q4 + c], kv[c], s4[k]);
+                        d4[k] = fmaf(sG[(i + k) * DH + part * Q4 + c], vv[c], d4[k]);
+                    }
                 }
-                s += __shfl_xor(s, 1, 64);
-                s += __shfl_xor(s, 2, 64);
-                dp += __shfl_xor(dp, 1, 64);
-                dp += __shfl_xor(dp, 2, 64);
-                float x = s * a.alpha;
-                if (RAB) x += sRab[rab_bucket(sQts[i], kts, a.nbuckets)];
+                const int ik = i + part;                       // this thread's query of the four
+                const float dp = quad_sum4(d4, part);
+                float x = quad_sum4(s4, part) * a.alpha;
+                if (RAB) x += sRab[rab_bucket(sQts[ik], kts, a.nbuckets)];
                 const float sg = 1.0f / (1.0f + expf(-x));
                 const float p = x * sg * inv_n;
                 const float ds = dp * sg * (1.0f + x * (1.0f - sg)) * inv_n;
-                if (visible(sQcode[i], sQts[i], qb + i, kcode, kts, kj)) {
+                const int vis = visible(sQcode[ik], sQts[ik], qb + ik, kcode, kts, kj) ? 1 : 0;
+                const float pk[4] = {quad_lane<0>(p), quad_lane<1>(p), quad_lane<2>(p), quad_lane<3>(p)};
+                const float gk[4] = {quad_lane<0>(ds), quad_lane<1>(ds), quad_lane<2>(ds), quad_lane<3>(ds)};
+                const int vk[4] = {quad_lane<0>(vis), quad_lane<1>(vis), quad_lane<2>(vis), quad_lane<3>(vis)};
+#pragma unroll
+                for (int k = 0; k < 4; k++)
 #pragma unroll
                     for (int c = 0; c < Q4; c++) {
-                        dv[c] = fmaf(p, sG[i * KP + part * Q4 + c], dv[c]);
-                        dk[c] = fmaf(ds, sQ[i * KP + part * Q4 + c], dk[c]);
+                        const float o = fmaf(pk[k], sG[(i + k) * DH + part * Q4 + c], dv[c]);
+                        const float e = fmaf(gk[k], sQ[(i + k) * DH + part * Q4 + c], dk[c]);
+                        dv[c] = vk[k] ? o : dv[c];
+                        dk[c] = vk[k] ? e : dk[c];
                     }
-                }
             }
         }
     }

@@ -252,6 +252,23 @@ __device__ __forceinline__ float dpp_add(float v) {
     return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 
+// Value of lane K of this lane's quad.
+template <int K>
+__device__ __forceinline__ int quad_lane(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x55 * K, 0xF, 0xF, false);
+}
+template <int K>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(quad_lane<K>(__float_as_int(v)));
+}
+// Sums of four values over the quad, (v0 + v1) + (v2 + v3); lane `part` gets that of v[part].
+__device__ __forceinline__ float quad_sum4(const float (&v)[4], int part) {
+    float t[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) t[k] = dpp_add<0x4E>(dpp_add<0xB1>(v[k]));
+    return part < 2 ? (part == 0 ? t[0] : t[1]) : (part == 2 ? t[2] : t[3]);
+}
+
 // Sum over the wave, equal in every lane: four DPP steps give each lane its 16-lane row sum
 // (quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror), then the four row
 // sums are read with v_readlane and added in a fixed order.
