@@ -287,6 +287,15 @@ mtgr_status_t mtgr_group_layernorm_bwd(const mtgr_gln_problem_t* p, const void* 
                                        float* dgamma, float* dbeta, void* workspace,
                                        size_t workspace_bytes, mtgr_stream_t stream);
 
+/* mtgr_group_layernorm_bwd without a gate, with a residual's gradient added to dx in fp32 before
+ * the one rounding: dx = dz + residual.  residual [T, d] (dtype), row stride ld_u; it may be dx
+ * itself when ld_u = ld_x. */
+mtgr_status_t mtgr_group_layernorm_bwd_add(const mtgr_gln_problem_t* p, const void* dy, const void* x,
+                                           const void* residual, const int8_t* group_ids,
+                                           const float* gamma, const float* mean, const float* rstd,
+                                           void* dx, float* dgamma, float* dbeta, void* workspace,
+                                           size_t workspace_bytes, mtgr_stream_t stream);
+
 /* Projection activation of the encoder layer built around the attention (Sec. 4.2: the
  * Group-LN'd input is projected to K, Q, V, U by MLPs; read here as one fused linear map
  * followed by SiLU, as in HSTU, with the GEMM left to a BLAS library):

@@ -561,11 +561,11 @@ mtgr_status_t mtgr_group_layernorm_fwd(const mtgr_gln_problem_t* p, const void* 
     return ok();
 }
 
-mtgr_status_t mtgr_group_layernorm_bwd(const mtgr_gln_problem_t* p, const void* dy, const void* x,
-                                       const void* u, const int8_t* group_ids, const float* gamma,
-                                       const float* mean, const float* rstd, void* dx, void* du,
-                                       float* dgamma, float* dbeta, void* workspace,
-                                       size_t workspace_bytes, mtgr_stream_t stream) {
+static mtgr_status_t gln_bwd(const mtgr_gln_problem_t* p, const void* dy, const void* x, const void* u,
+                             const void* res, const int8_t* group_ids, const float* gamma,
+                             const float* mean, const float* rstd, void* dx, void* du,
+                             float* dgamma, float* dbeta, void* workspace,
+                             size_t workspace_bytes, mtgr_stream_t stream) {
     mtgr_status_t st = check_gln(p);
     if (st != MTGR_SUCCESS) return st;
     REQUIRE_PTR(gamma, "gamma");
@@ -595,6 +595,7 @@ mtgr_status_t mtgr_group_layernorm_bwd(const mtgr_gln_problem_t* p, const void* 
     a.dy = dy;
     a.x = x;
     a.u = u;
+    a.res = res;
     a.gid = group_ids;
     a.gamma = gamma;
     a.mean = const_cast<float*>(mean);
@@ -607,6 +608,25 @@ mtgr_status_t mtgr_group_layernorm_bwd(const mtgr_gln_problem_t* p, const void* 
     hipError_t e = mtgr::launch_gln_bwd(a, p->dtype == MTGR_DTYPE_BF16, (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "group layernorm backward");
     return ok();
+}
+
+mtgr_status_t mtgr_group_layernorm_bwd(const mtgr_gln_problem_t* p, const void* dy, const void* x,
+                                       const void* u, const int8_t* group_ids, const float* gamma,
+                                       const float* mean, const float* rstd, void* dx, void* du,
+                                       float* dgamma, float* dbeta, void* workspace,
+                                       size_t workspace_bytes, mtgr_stream_t stream) {
+    return gln_bwd(p, dy, x, u, nullptr, group_ids, gamma, mean, rstd, dx, du, dgamma, dbeta, workspace,
+                   workspace_bytes, stream);
+}
+
+mtgr_status_t mtgr_group_layernorm_bwd_add(const mtgr_gln_problem_t* p, const void* dy, const void* x,
+                                           const void* residual, const int8_t* group_ids,
+                                           const float* gamma, const float* mean, const float* rstd,
+                                           void* dx, float* dgamma, float* dbeta, void* workspace,
+                                           size_t workspace_bytes, mtgr_stream_t stream) {
+    if (p && p->num_tokens > 0) REQUIRE_PTR(residual, "residual");
+    return gln_bwd(p, dy, x, nullptr, residual, group_ids, gamma, mean, rstd, dx, nullptr, dgamma, dbeta,
+                   workspace, workspace_bytes, stream);
 }
 
 static mtgr_status_t check_pointwise(int64_t rows, int32_t cols, mtgr_dtype_t dtype,

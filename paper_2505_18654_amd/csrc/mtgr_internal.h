@@ -89,6 +89,7 @@ struct GlnArgs {
     float* mean;
     float* rstd;
     const void* dy;
+    const void* res;    // backward without a gate: added to dx (row stride ld_u)
     void* dx;
     void* du;
     float* dgamma;

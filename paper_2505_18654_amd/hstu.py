@@ -46,6 +46,7 @@ EXPORTED = (
     "mtgr_hstu_attn_workspace_size", "mtgr_hstu_attn_plan", "mtgr_hstu_attn_fwd", "mtgr_hstu_attn_bwd",
     "mtgr_hstu_attn_fwd_noalloc", "mtgr_hstu_attn_fwd_cached",
     "mtgr_group_layernorm_workspace_size", "mtgr_group_layernorm_fwd", "mtgr_group_layernorm_bwd",
+    "mtgr_group_layernorm_bwd_add",
     "mtgr_bias_silu_fwd", "mtgr_bias_silu_bwd", "mtgr_add", "mtgr_gemm_workspace_size", "mtgr_gemm_bf16",
     "mtgr_debug_validate_inputs", "mtgr_debug_clock_probe", "mtgr_status_string", "mtgr_last_error_message", "mtgr_version",
     "mtgr_embedding_init", "mtgr_embedding_dedup_workspace_size", "mtgr_embedding_dedup",
@@ -116,6 +117,7 @@ def lib() -> ctypes.CDLL:
         L.mtgr_group_layernorm_workspace_size.argtypes = [G, ctypes.c_int, ctypes.POINTER(sz)]
         L.mtgr_group_layernorm_fwd.argtypes = [G, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.mtgr_group_layernorm_bwd.argtypes = [G, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.mtgr_group_layernorm_bwd_add.argtypes = [G, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.mtgr_debug_validate_inputs.argtypes = [P, vp, vp, vp, i32, vp, sz, vp]
         i64 = ctypes.c_int64
         L.mtgr_bias_silu_fwd.argtypes = [i64, i32, ctypes.c_int, vp, i64, vp, vp, i64, vp]
@@ -259,6 +261,14 @@ def mtgr_group_layernorm_bwd(problem, dy, x, u, group_ids, gamma, mean, rstd, dx
                                           _ptr(group_ids), _ptr(gamma), _ptr(mean), _ptr(rstd),
                                           _ptr(dx), _ptr(du), _ptr(dgamma), _ptr(dbeta),
                                           _ptr(workspace), int(workspace_bytes), _stream(stream)))
+
+
+def mtgr_group_layernorm_bwd_add(problem, dy, x, residual, group_ids, gamma, mean, rstd, dx, dgamma, dbeta,
+                                 workspace=None, workspace_bytes=0, stream=None) -> None:
+    _check(lib().mtgr_group_layernorm_bwd_add(ctypes.byref(problem), _ptr(dy), _ptr(x), _ptr(residual),
+                                              _ptr(group_ids), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dx),
+                                              _ptr(dgamma), _ptr(dbeta), _ptr(workspace), int(workspace_bytes),
+                                              _stream(stream)))
 
 
 def mtgr_bias_silu_fwd(rows, cols, dtype, h, ld_h, bias, out, ld_out, stream=None) -> None:

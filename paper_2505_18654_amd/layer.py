@@ -9,7 +9,7 @@ Every step runs in this package's HIP kernels through the C ABI: the projection 
 bias + SiLU in its epilogue (it keeps the pre-activation for the backward), the output product
 with bias + residual in its epilogue, the input-gradient products (A B^T), the weight-gradient
 products (A^T B, split over tokens) with the bias gradients as fused column sums, Group-LN,
-the attention and the residual add of the input gradient.  Q, K, V, U are column views of the
+the attention and the residual add of the input gradient (in the Group-LN's backward).  Q, K, V, U are column views of the
 one [T, 4d] activation, which the kernels take with their token stride, and their gradients are
 written into the same layout, so the backward's input-projection products read one [T, 4d]
 gradient.  torch only allocates.
@@ -89,8 +89,12 @@ def layer_bwd(dx_out: torch.Tensor, ctx: dict, jag: ops.Jagged, P: LayerParams, 
     g["b_in"] = torch.empty(4 * d, dtype=torch.float32, device=x.device)
     g["w_in"] = ops.gemm(xt, da, "tn", colsum=g["b_in"])
     dxt = ops.gemm(da, P.w_in, "nt")
-    dx, _, g["gamma_in"], g["beta_in"] = ops.gln_bwd(dxt, x, None, jag.seg, P.gamma_in, ctx["m0"], ctx["r0"], eps)
-    g["x"] = ops.add(dx, dx_out)
+    # One pass forms dX = dX_gln + dX', unless the caller wants dX_gln too or X is a view with gaps
+    # between its rows (the Group-LN's dx has the strides of x, dX is dense).
+    one_pass = keep is None and x.is_contiguous()
+    dx, _, g["gamma_in"], g["beta_in"] = ops.gln_bwd(dxt, x, None, jag.seg, P.gamma_in, ctx["m0"], ctx["r0"], eps,
+                                                     residual=dx_out if one_pass else None)
+    g["x"] = dx if one_pass else ops.add(dx, dx_out)
     if keep is not None:
         keep.update(dh=da, dxt=dxt, dx_gln=dx)
     return g

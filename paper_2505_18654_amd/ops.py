@@ -200,8 +200,12 @@ def gln_fwd(x, u, group_ids, gamma, beta, eps: float = 1e-5, y=None, stats=None)
     return y, mean, rstd
 
 
-def gln_bwd(dy, x, u, group_ids, gamma, mean, rstd, eps: float = 1e-5, grads=None, workspace=None):
-    """Gate + Group-LN backward: returns (dx, du-or-None, dgamma, dbeta)."""
+def gln_bwd(dy, x, u, group_ids, gamma, mean, rstd, eps: float = 1e-5, grads=None, workspace=None,
+            residual=None):
+    """Gate + Group-LN backward: returns (dx, du-or-None, dgamma, dbeta).  `residual` (only without
+    a gate) is added to dx before its rounding."""
+    if residual is not None and u is not None:
+        raise ValueError("a residual goes with the Group-LN without a gate")
     T, d = x.shape
     if grads is None:
         dx = _like_layout(x)
@@ -211,12 +215,19 @@ def gln_bwd(dy, x, u, group_ids, gamma, mean, rstd, eps: float = 1e-5, grads=Non
     else:
         dx, du, dgamma, dbeta = grads
     p = hstu.gln_problem(T, d, gamma.shape[0], _dtype_code(x), eps, _token_stride(x, d),
-                         _token_stride(u, d) if u is not None else d, _token_stride(dy, d))
+                         _token_stride(residual if u is None else u, d) if u is not None or residual is not None else d,
+                         _token_stride(dy, d))
     if _token_stride(dx, d) != p.ld_x or (du is not None and _token_stride(du, d) != p.ld_u):
         raise ValueError("gradients must share the layout of x, u")
     if workspace is None:
         n = hstu.mtgr_group_layernorm_workspace_size(p, True)
         workspace = torch.empty(max(n, 256), dtype=torch.uint8, device=x.device)
+    if residual is not None:
+        if residual.shape != x.shape or residual.dtype != x.dtype:
+            raise ValueError("the residual has the shape and type of x")
+        hstu.mtgr_group_layernorm_bwd_add(p, dy, x, residual, group_ids, gamma, mean, rstd, dx, dgamma, dbeta,
+                                          workspace, workspace.numel())
+        return dx, None, dgamma, dbeta
     hstu.mtgr_group_layernorm_bwd(p, dy, x, u, group_ids, gamma, mean, rstd, dx, du, dgamma, dbeta,
                                   workspace, workspace.numel())
     return dx, du, dgamma, dbeta
