@@ -257,6 +257,18 @@ mtgr_status_t mtgr_hstu_attn_bwd(const mtgr_hstu_problem_t* p, const int32_t* of
                                  const void* dout, void* dq, void* dk, void* dv, float* drab,
                                  void* workspace, size_t workspace_bytes, mtgr_stream_t stream);
 
+/* mtgr_hstu_attn_bwd where q, k, v are activations silu(h + bias): writes the gradients of h, i.e.
+ * dhq = dq silu'(h_q + bias_q) with dq rounded to the dtype first, and so on, bit for bit what
+ * mtgr_bias_silu_bwd makes of dq, dk, dv.  h [T, 3 H dh] holds q's, k's and v's pre-activations side by
+ * side (bf16, row stride ld_h, 16-byte rows), bias [3 H dh] fp32 or NULL.  bf16 with head_dim 32, 64
+ * or 128. */
+mtgr_status_t mtgr_hstu_attn_bwd_act(const mtgr_hstu_problem_t* p, const int32_t* offsets,
+                                     const int8_t* seg, const int32_t* ts, const void* q, const void* k,
+                                     const void* v, const float* rab, const void* dout, const void* h,
+                                     int64_t ld_h, const float* bias, void* dhq, void* dhk, void* dhv,
+                                     float* drab, void* workspace, size_t workspace_bytes,
+                                     mtgr_stream_t stream);
+
 /* Bytes of device workspace for the Group-LN calls: 0 for the forward; the backward
  * keeps per-workgroup dgamma/dbeta partials (about 512 x 2 G d floats at most). */
 mtgr_status_t mtgr_group_layernorm_workspace_size(const mtgr_gln_problem_t* p, int backward,

@@ -387,11 +387,11 @@ mtgr_status_t mtgr_hstu_attn_fwd_cached(const mtgr_hstu_problem_t* p, const int3
     return ok();
 }
 
-mtgr_status_t mtgr_hstu_attn_bwd(const mtgr_hstu_problem_t* p, const int32_t* offsets,
-                                 const int8_t* seg, const int32_t* ts, const void* q, const void* k,
-                                 const void* v, const float* rab, const void* dout, void* dq,
-                                 void* dk, void* dv, float* drab, void* workspace,
-                                 size_t workspace_bytes, mtgr_stream_t stream) {
+static mtgr_status_t attn_bwd(const mtgr_hstu_problem_t* p, const int32_t* offsets,
+                              const int8_t* seg, const int32_t* ts, const void* q, const void* k,
+                              const void* v, const float* rab, const void* dout, const void* act_h,
+                              int64_t ld_act, const float* act_bias, void* dq, void* dk, void* dv, float* drab,
+                              void* workspace, size_t workspace_bytes, mtgr_stream_t stream) {
     mtgr_status_t st = check_attn_common(p, offsets, seg, ts, rab, workspace, workspace_bytes);
     if (st != MTGR_SUCCESS) return st;
     if (p->flags & MTGR_FWD_CAND_ROWS)
@@ -460,11 +460,42 @@ mtgr_status_t mtgr_hstu_attn_bwd(const mtgr_hstu_problem_t* p, const int32_t* of
     a.dk = dk;
     a.dv = dv;
     a.drab = drab_out;
+    a.act_h = act_h;
+    a.act_bias = act_bias;
+    a.ld_act = ld_act;
     hipError_t e = !vec ? mtgr::launch_attn_bwd_bf16(a, p->head_dim, (int)L.slots, plan, s)
                         : mtgr::launch_attn_bwd_vec(a, p->dtype == MTGR_DTYPE_BF16, p->head_dim, (int)L.slots,
                                                     want_dq, want_dkdv, s);
     if (e != hipSuccess) return device_fail(e, "attention backward");
     return ok();
+}
+
+mtgr_status_t mtgr_hstu_attn_bwd(const mtgr_hstu_problem_t* p, const int32_t* offsets,
+                                 const int8_t* seg, const int32_t* ts, const void* q, const void* k,
+                                 const void* v, const float* rab, const void* dout, void* dq,
+                                 void* dk, void* dv, float* drab, void* workspace,
+                                 size_t workspace_bytes, mtgr_stream_t stream) {
+    return attn_bwd(p, offsets, seg, ts, q, k, v, rab, dout, nullptr, 0, nullptr, dq, dk, dv, drab, workspace,
+                    workspace_bytes, stream);
+}
+
+mtgr_status_t mtgr_hstu_attn_bwd_act(const mtgr_hstu_problem_t* p, const int32_t* offsets,
+                                     const int8_t* seg, const int32_t* ts, const void* q, const void* k,
+                                     const void* v, const float* rab, const void* dout, const void* h,
+                                     int64_t ld_h, const float* bias, void* dhq, void* dhk, void* dhv,
+                                     float* drab, void* workspace, size_t workspace_bytes,
+                                     mtgr_stream_t stream) {
+    if (!p) return fail(MTGR_ERROR_NULL_POINTER, "problem is NULL");
+    if (vec_path(p))
+        return fail(MTGR_ERROR_UNSUPPORTED, "the backward through the activation needs bf16 and head_dim >= 32");
+    if (p->num_users > 0 && p->total_tokens > 0) {
+        REQUIRE_PTR(h, "h");
+        if (ld_h < 3ll * p->num_heads * p->head_dim || ld_h % 8 != 0)
+            return fail(MTGR_ERROR_INVALID_ARGUMENT, "ld_h = %lld (needs >= 3 H dh and a multiple of 8)", (long long)ld_h);
+        if (((uintptr_t)bias & 3u) != 0) return fail(MTGR_ERROR_INVALID_ARGUMENT, "bias is not 4-byte aligned");
+    }
+    return attn_bwd(p, offsets, seg, ts, q, k, v, rab, dout, h, ld_h, bias, dhq, dhk, dhv, drab, workspace,
+                    workspace_bytes, stream);
 }
 
 }  // extern "C"

@@ -251,25 +251,30 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_vec_kernel(AttnArgs a) {
 
 // The relative bias enters the scores of both kernels (RAB_IN).  drab (a.drab) is formed by the
 // dK/dV kernel when it runs, else by the recomputing dQ kernel.
-template <int DH, bool RAB_IN>
-static hipError_t bwd_bf16_dh(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
+template <int DH, bool RAB_IN, bool ACT>
+static hipError_t bwd_bf16_act(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
     if (plan.dkdv) {
-        if (plan.store_ds) attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, true><<<slots, 256, 0, s>>>(a);
-        else attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, false><<<slots, 256, 0, s>>>(a);
+        if (plan.store_ds) attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, true, ACT><<<slots, 256, 0, s>>>(a);
+        else attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, false, ACT><<<slots, 256, 0, s>>>(a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (plan.dq_from_ds) {
-        attn_bwd_dq_ds_bf16_kernel<DH><<<slots, 256, 0, s>>>(a);
+        attn_bwd_dq_ds_bf16_kernel<DH, ACT><<<slots, 256, 0, s>>>(a);
         return hipGetLastError();
     }
     if (plan.dq_recompute) {
         AttnArgs b = a;
         if (plan.dkdv) b.drab = nullptr;
-        attn_bwd_dq_bf16_kernel<DH, RAB_IN><<<slots, 256, 0, s>>>(b);
+        attn_bwd_dq_bf16_kernel<DH, RAB_IN, ACT><<<slots, 256, 0, s>>>(b);
         return hipGetLastError();
     }
     return hipSuccess;
+}
+
+template <int DH, bool RAB_IN>
+static hipError_t bwd_bf16_dh(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
+    return a.act_h ? bwd_bf16_act<DH, RAB_IN, true>(a, slots, plan, s) : bwd_bf16_act<DH, RAB_IN, false>(a, slots, plan, s);
 }
 
 template <int DH, bool RAB_IN, class E>

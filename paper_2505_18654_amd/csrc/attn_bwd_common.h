@@ -18,6 +18,61 @@ __device__ __forceinline__ void zero(floatx16& x) {
     for (int r = 0; r < 16; r++) x[r] = 0.f;
 }
 
+// Gradient rows on their way out: each wave's 32 staged rows (bf16, swizzled) from row0 of the
+// user on go to columns h DH .. of dst, 16 bytes per lane and step.  With ACT they pass through
+// the projection's activation (part 0, 1, 2: q, k, v): dh = da silu'(h + b), from the rounded da, as
+// the pointwise kernel forms it.  In here that costs a read of h; as a pass of its own, bound by
+// memory, it wrote and read da once more (1.2 GB of a layer step on 79,372 rows x 1,024: 5,823 ->
+// 5,696 us; 128 users, d = 512, with a bias: 1,863 -> 1,771 us).
+template <int DH, bool ACT>
+struct GradRows {
+    static constexpr int CPR = DH / 8, N = 32 * CPR / 64;
+    u32x4_nt hrow[N];
+    float bias[8];
+    // the rows of h, issued before the gradients are staged (rows past the user's end clamp)
+    __device__ __forceinline__ void load(const AttnArgs& a, int part, int ob, int nb, int h, int row0, int lane) {
+        if (!ACT) return;
+        const int col = (part * a.heads + h) * DH + 8 * (lane % CPR);
+#pragma unroll
+        for (int i = 0; i < N; i++) {
+            const int r = min(row0 + (lane + 64 * i) / CPR, nb - 1);
+            hrow[i] = __builtin_nontemporal_load(
+                (const u32x4_nt*)((const uint16_t*)a.act_h + (long long)(ob + r) * a.ld_act + col));
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e++) bias[e] = 0.f;
+        if (a.act_bias) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) bias[e] = a.act_bias[col + e];
+        }
+    }
+    __device__ __forceinline__ void store(const AttnArgs& a, uint16_t* dst, long long ld, const uint16_t* sO, int ob,
+                                          int nb, int h, int row0, int lane) const {
+#pragma unroll
+        for (int i = 0; i < N; i++) {
+            const int c = lane + 64 * i, row = c / CPR, cc = c % CPR, r = row0 + row;
+            if (r >= nb) continue;
+            uint16_t* out = dst + (long long)(ob + r) * ld + h * DH + cc * 8;
+            const uint16_t* src = &sO[8 * tile_chunk<CPR>(row, cc)];
+            if (!ACT) {
+                store_nt16(out, src);
+                continue;
+            }
+            const u32x4_nt g = *(const u32x4_nt*)src;
+            uint32_t o[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const uint32_t gw = g[j], hw = hrow[i][j];
+                o[j] = pack_bf16x2(silu_grad(__uint_as_float(gw << 16), __uint_as_float(hw << 16) + bias[2 * j]),
+                                   silu_grad(__uint_as_float(gw & 0xffff0000u),
+                                             __uint_as_float(hw & 0xffff0000u) + bias[2 * j + 1]));
+            }
+            const uint4 v = make_uint4(o[0], o[1], o[2], o[3]);
+            store_nt16(out, &v);
+        }
+    }
+};
+
 // drab histogram of one workgroup in LDS.  Log-time buckets put most (query, key) pairs of a
 // tile into a handful of buckets, so one histogram would serialise the 64 lanes of each LDS
 // atomic.  Lane l adds into copy l % 32 (at most two lanes of an instruction share a copy),
@@ -75,11 +130,11 @@ __device__ __forceinline__ void hist_finish(float* hist, int nb, float scale, fl
 }
 }  // namespace bwd
 
-template <int DH, bool RAB>
+template <int DH, bool RAB, bool ACT>
 __global__ void attn_bwd_dq_bf16_kernel(AttnArgs a);
-template <int DH, bool RAB, bool STORE>
+template <int DH, bool RAB, bool STORE, bool ACT>
 __global__ void attn_bwd_dkdv_bf16_kernel(AttnArgs a);
-template <int DH>
+template <int DH, bool ACT>
 __global__ void attn_bwd_dq_ds_bf16_kernel(AttnArgs a);
 
 }  // namespace mtgr

@@ -18,7 +18,7 @@ using bwd::zero;
 // complete in issue order), serialising copy and compute.
 // With STORE it also writes dS (bf16, the A operand of its dK product, masked but without the
 // factor 1 / n_b) as 64 x 64 blocks for the dQ-from-dS kernel; it forms drab when a.drab is set.
-template <int DH, bool RAB, bool STORE>
+template <int DH, bool RAB, bool STORE, bool ACT>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) {
     constexpr int CPR = DH / 8, KSTEPS = DH / 16, DBLK = DH / 32, UNIT = 32 * DH;
     __shared__ __align__(16) uint16_t sK[BM * DH];
@@ -357,6 +357,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) 
     const float dk_scale = alpha * inv_n, dv_scale = RAB ? inv_n : alpha * inv_n;
     uint16_t* DK = (uint16_t*)a.dk;
     uint16_t* DV = (uint16_t*)a.dv;
+    // Through the activation: the rows of h come in before the staging, at head_dim 128 after it,
+    // with the kernel's arguments read again (kept across the loop, at 256 VGPRs, they made it spill
+    // two V fragments: 64 users with 66 k tokens, 8 heads, the layer step gained nothing).
+    constexpr bool PRELOAD = DH <= 64;
+    bwd::GradRows<DH, ACT && PRELOAD> rows[2];
+#pragma unroll
+    for (int which = 0; which < 2; which++) rows[which].load(a, 1 + which, ob, nb, h, k0 + w * 32, lane);
 #pragma unroll
     for (int which = 0; which < 2; which++) {
         __syncthreads();
@@ -375,26 +382,40 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) 
         __syncthreads();
         uint16_t* dst = which == 0 ? DK : DV;
         const long long ld = which == 0 ? a.ld_k : a.ld_v;
-#pragma unroll
-        for (int i = 0; i < 32 * CPR / 64; i++) {
-            const int c = lane + 64 * i, row = c / CPR, cc = c % CPR;
-            const int kr = k0 + w * 32 + row;
-            if (kr < nb)
-                store_nt16(dst + (long long)(ob + kr) * ld + h * DH + cc * 8, &sO[8 * tile_chunk<CPR>(row, cc)]);
+        if constexpr (PRELOAD || !ACT) {
+            rows[which].store(a, dst, ld, sO, ob, nb, h, k0 + w * 32, lane);
+        } else {
+            const AttnArgs* args = (const AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(args));
+            bwd::GradRows<DH, ACT> late;
+            late.load(*args, 1 + which, ob, nb, h, k0 + w * 32, lane);
+            late.store(*args, dst, ld, sO, ob, nb, h, k0 + w * 32, lane);
         }
     }
 }
 
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, true, true>(AttnArgs);
 }  // namespace mtgr

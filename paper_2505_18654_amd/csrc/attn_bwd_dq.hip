@@ -8,7 +8,7 @@ using bwd::ldg16;
 using bwd::zero;
 
 // ------------------------------------------------------------------ dQ (+ drab), bf16
-template <int DH, bool RAB>
+template <int DH, bool RAB, bool ACT>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     constexpr int CPR = DH / 8, KSTEPS = DH / 16, DBLK = DH / 32, TILE = BN * DH;
     __shared__ __align__(16) uint16_t sK0[TILE];
@@ -181,6 +181,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
         bwd::hist_finish(sHist, a.nbuckets, inv_n, a.drab + h * a.nbuckets, tid);
     }
     uint16_t* sO = (w < 2 ? sK0 : sK1) + (w & 1) * 32 * DH;
+    bwd::GradRows<DH, ACT> rows;
+    rows.load(a, 0, ob, nb, h, q0 + w * 32, lane);
     const float dq_scale = alpha * inv_n;
 #pragma unroll
     for (int d = 0; d < DBLK; d++) {
@@ -194,19 +196,19 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     }
     __syncthreads();
     uint16_t* DQ = (uint16_t*)a.dq;
-#pragma unroll
-    for (int i = 0; i < 32 * CPR / 64; i++) {
-        const int c = lane + 64 * i, row = c / CPR, cc = c % CPR;
-        const int qr = q0 + w * 32 + row;
-        if (qr < nb)
-            store_nt16(DQ + (long long)(ob + qr) * a.ld_q + h * DH + cc * 8, &sO[8 * tile_chunk<CPR>(row, cc)]);
-    }
+    rows.store(a, DQ, a.ld_q, sO, ob, nb, h, q0 + w * 32, lane);
 }
 
-template __global__ void attn_bwd_dq_bf16_kernel<32, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<32, true>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<64, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<64, true>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<128, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<128, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, false, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, false, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, true, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, true, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, false, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, false, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, true, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, true, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, false, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, false, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, true, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, true, true>(AttnArgs);
 }  // namespace mtgr

@@ -17,7 +17,7 @@ using bwd::zero;
 // by pointing each supplier lane at the fragment chunk of (key, 4 queries) that the transpose
 // must deliver.  A block exists only if the dK/dV kernel visited its (64 queries, 128 keys)
 // pair; otherwise all its pairs are masked and the wave skips it.
-template <int DH>
+template <int DH, bool ACT>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_ds_bf16_kernel(AttnArgs a) {
     constexpr int CPR = DH / 8, DBLK = DH / 32, TILE = BN * DH, DSB = 64 * 64;
     __shared__ __align__(16) uint16_t sK0[TILE];
@@ -144,6 +144,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_ds_bf16_kernel(AttnArgs a)
     __syncthreads();
 
     uint16_t* sO = (w < 2 ? sK0 : sK1) + (w & 1) * 32 * DH;
+    bwd::GradRows<DH, ACT> rows;
+    rows.load(a, 0, ob, nb, h, q0 + w * 32, lane);
 #pragma unroll
     for (int d = 0; d < DBLK; d++) {
 #pragma unroll
@@ -156,16 +158,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_ds_bf16_kernel(AttnArgs a)
     }
     __syncthreads();
     uint16_t* DQ = (uint16_t*)a.dq;
-#pragma unroll
-    for (int i = 0; i < 32 * CPR / 64; i++) {
-        const int c = lane + 64 * i, row = c / CPR, cc = c % CPR;
-        const int qr = q0 + w * 32 + row;
-        if (qr < nb)
-            store_nt16(DQ + (long long)(ob + qr) * a.ld_q + h * DH + cc * 8, &sO[8 * tile_chunk<CPR>(row, cc)]);
-    }
+    rows.store(a, DQ, a.ld_q, sO, ob, nb, h, q0 + w * 32, lane);
 }
 
-template __global__ void attn_bwd_dq_ds_bf16_kernel<32>(AttnArgs);
-template __global__ void attn_bwd_dq_ds_bf16_kernel<64>(AttnArgs);
-template __global__ void attn_bwd_dq_ds_bf16_kernel<128>(AttnArgs);
+template __global__ void attn_bwd_dq_ds_bf16_kernel<32, false>(AttnArgs);
+template __global__ void attn_bwd_dq_ds_bf16_kernel<32, true>(AttnArgs);
+template __global__ void attn_bwd_dq_ds_bf16_kernel<64, false>(AttnArgs);
+template __global__ void attn_bwd_dq_ds_bf16_kernel<64, true>(AttnArgs);
+template __global__ void attn_bwd_dq_ds_bf16_kernel<128, false>(AttnArgs);
+template __global__ void attn_bwd_dq_ds_bf16_kernel<128, true>(AttnArgs);
 }  // namespace mtgr

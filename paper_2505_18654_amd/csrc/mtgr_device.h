@@ -228,6 +228,12 @@ __device__ __forceinline__ void store_nt8(void* dst, uint32_t lo, uint32_t hi) {
     __builtin_nontemporal_store(v, (u32x2_nt*)dst);
 }
 
+// g silu'(z), silu'(z) = sg (1 + z (1 - sg)) with sg = sigmoid(z).
+__device__ __forceinline__ float silu_grad(float g, float z) {
+    const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
+    return g * sg * (1.0f + z * (1.0f - sg));
+}
+
 // Element access of the vector-ALU kernels, which store either fp32 or bf16 and compute in fp32.
 __device__ __forceinline__ float ld_elem(const float* p, long long i) { return p[i]; }
 __device__ __forceinline__ float ld_elem(const uint16_t* p, long long i) { return bf16_to_f32(p[i]); }

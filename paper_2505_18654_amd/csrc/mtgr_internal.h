@@ -43,6 +43,11 @@ struct AttnArgs {
     const int* tok_code_k;    // [Tc] cache token codes (from the cache's plan)
     const int4* summ_k;       // [B][ntile_k] cache tile summaries (from the cache's plan)
     int ntile_k;
+    // Backward through the projection's activation: q, k, v = silu(act_h + act_bias), [T, 3 H dh] as
+    // q | k | v, row stride ld_act; act_h null: gradients of q, k, v themselves.
+    const void* act_h;
+    const float* act_bias;
+    long long ld_act;
 };
 
 // Number of physical work-list slots for tiles of `bm` rows (see build_schedule).

@@ -69,8 +69,8 @@ __global__ __launch_bounds__(256) void bias_silu_kernel(long long rows, int cols
             if (BWD) C::load(g, r * ld_g + c, o);
 #pragma unroll
             for (int i = 0; i < N; i++) {
-                const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z[i]));
-                o[i] = BWD ? o[i] * sg * (1.0f + z[i] * (1.0f - sg)) : z[i] * sg;
+                if (BWD) o[i] = silu_grad(o[i], z[i]);
+                else o[i] = z[i] * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z[i]));
             }
             C::store(out, r * ld_out + c, o);
         }

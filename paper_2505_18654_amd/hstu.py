@@ -44,6 +44,7 @@ MTGR_EMB_STATE_NEXT_ROW, MTGR_EMB_STATE_FREE_TOP, MTGR_EMB_STATE_NUM_KEYS, MTGR_
 
 EXPORTED = (
     "mtgr_hstu_attn_workspace_size", "mtgr_hstu_attn_plan", "mtgr_hstu_attn_fwd", "mtgr_hstu_attn_bwd",
+    "mtgr_hstu_attn_bwd_act",
     "mtgr_hstu_attn_fwd_noalloc", "mtgr_hstu_attn_fwd_cached",
     "mtgr_group_layernorm_workspace_size", "mtgr_group_layernorm_fwd", "mtgr_group_layernorm_bwd",
     "mtgr_group_layernorm_bwd_add",
@@ -114,6 +115,8 @@ def lib() -> ctypes.CDLL:
         L.mtgr_hstu_attn_fwd_cached.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, P, vp, vp, vp, vp, vp, sz,
                                                 vp, sz, vp]
         L.mtgr_hstu_attn_bwd.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.mtgr_hstu_attn_bwd_act.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_int64, vp, vp, vp, vp, vp,
+                                             vp, sz, vp]
         L.mtgr_group_layernorm_workspace_size.argtypes = [G, ctypes.c_int, ctypes.POINTER(sz)]
         L.mtgr_group_layernorm_fwd.argtypes = [G, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.mtgr_group_layernorm_bwd.argtypes = [G, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
@@ -240,6 +243,14 @@ def mtgr_hstu_attn_bwd(problem, offsets, seg, ts, q, k, v, rab, dout, dq, dk, dv
                                     _ptr(q), _ptr(k), _ptr(v), _ptr(rab), _ptr(dout), _ptr(dq),
                                     _ptr(dk), _ptr(dv), _ptr(drab), _ptr(workspace),
                                     int(workspace_bytes), _stream(stream)))
+
+
+def mtgr_hstu_attn_bwd_act(problem, offsets, seg, ts, q, k, v, rab, dout, h, ld_h, bias, dhq, dhk, dhv, drab, workspace,
+                           workspace_bytes, stream=None) -> None:
+    _check(lib().mtgr_hstu_attn_bwd_act(ctypes.byref(problem), _ptr(offsets), _ptr(seg), _ptr(ts),
+                                        _ptr(q), _ptr(k), _ptr(v), _ptr(rab), _ptr(dout), _ptr(h), int(ld_h),
+                                        _ptr(bias), _ptr(dhq), _ptr(dhk), _ptr(dhv), _ptr(drab), _ptr(workspace),
+                                        int(workspace_bytes), _stream(stream)))
 
 
 def mtgr_group_layernorm_workspace_size(problem: GlnProblem, backward: bool = False) -> int:

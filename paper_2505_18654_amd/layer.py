@@ -9,7 +9,8 @@ Every step runs in this package's HIP kernels through the C ABI: the projection 
 bias + SiLU in its epilogue (it keeps the pre-activation for the backward), the output product
 with bias + residual in its epilogue, the input-gradient products (A B^T), the weight-gradient
 products (A^T B, split over tokens) with the bias gradients as fused column sums, Group-LN,
-the attention and the residual add of the input gradient (in the Group-LN's backward).  Q, K, V, U are column views of the
+the attention (whose backward goes on through the SiLU of the projection) and the residual add of the
+input gradient (in the Group-LN's backward).  Q, K, V, U are column views of the
 one [T, 4d] activation, which the kernels take with their token stride, and their gradients are
 written into the same layout, so the backward's input-projection products read one [T, 4d]
 gradient.  torch only allocates.
@@ -79,13 +80,19 @@ def layer_bwd(dx_out: torch.Tensor, ctx: dict, jag: ops.Jagged, P: LayerParams, 
                 grads=(do.view(T, d), du, dgam, dbet))
     g["gamma"], g["beta"] = dgam, dbet
     drab = torch.empty_like(rab) if (rab is not None and need_drab) else None
+    # The attention backward forms the gradients of the pre-activations of Q, K, V itself (da becomes
+    # dh there), unless the caller wants da too or the vector kernels run (head_dim 16).
+    fused = keep is None and d // heads >= 32
     ops.attn_bwd(q, k, v, do, jag, rab, alpha, need_drab=drab is not None, grads=(dq, dk, dv, drab),
-                 workspace=workspace, planned=planned)
+                 workspace=workspace, planned=planned, act=(h[:, :3 * d], P.b_in[:3 * d]) if fused else None)
     if drab is not None:
         g["rab"] = drab
     if keep is not None:
         keep.update(dy=dy, do=do, da=da.clone())
-    hstu.mtgr_bias_silu_bwd(T, 4 * d, ops._dtype_code(h), h, 4 * d, P.b_in, da, 4 * d, da, 4 * d)
+    if fused:
+        hstu.mtgr_bias_silu_bwd(T, d, ops._dtype_code(h), h[:, 3 * d:], 4 * d, P.b_in[3 * d:], du, 4 * d, du, 4 * d)
+    else:
+        hstu.mtgr_bias_silu_bwd(T, 4 * d, ops._dtype_code(h), h, 4 * d, P.b_in, da, 4 * d, da, 4 * d)
     g["b_in"] = torch.empty(4 * d, dtype=torch.float32, device=x.device)
     g["w_in"] = ops.gemm(xt, da, "tn", colsum=g["b_in"])
     dxt = ops.gemm(da, P.w_in, "nt")

@@ -154,12 +154,15 @@ def attn_fwd_cached(q, k, v, jag: Jagged, cache: UserCache, rab=None, alpha: flo
 
 
 def attn_bwd(q, k, v, dout, jag: Jagged, rab=None, alpha: float = 1.0, need_drab: bool = True,
-             grads=None, workspace=None, planned: bool = False, parts: str = "all"):
+             grads=None, workspace=None, planned: bool = False, parts: str = "all", act=None):
     """Backward of Eq. 5: returns (dq, dk, dv, drab-or-None).
 
     parts: "all"; "dq" or "dkdv" (one side only); or the two halves of the stored-dS path as
     two calls on one backward-size workspace: "dkdv_keep_ds" (dk, dv, drab and the dS blocks)
-    then "dq_from_ds" (dq from them; drab is not formed again)."""
+    then "dq_from_ds" (dq from them; drab is not formed again).
+
+    act = (h, bias), h [T, 3 H dh] as q | k | v: q, k, v are silu(h + bias), and the gradients returned
+    are those of h (bf16, head_dim >= 32)."""
     flags = (hstu.MTGR_ATTN_PLANNED if planned else 0) | {
         "all": 0, "dq": hstu.MTGR_BWD_SKIP_DKDV, "dkdv": hstu.MTGR_BWD_SKIP_DQ,
         "dkdv_keep_ds": hstu.MTGR_BWD_SKIP_DQ | hstu.MTGR_BWD_KEEP_DS,
@@ -179,6 +182,14 @@ def attn_bwd(q, k, v, dout, jag: Jagged, rab=None, alpha: float = 1.0, need_drab
         raise ValueError("gradients must share the layout of q, k, v")
     if workspace is None:
         workspace = workspace_for(p, q.device, backward=True)
+    if act is not None:
+        h, bias = act
+        if h.shape != (q.shape[0], 3 * row) or h.dtype != q.dtype or \
+                (bias is not None and (bias.shape != (3 * row,) or bias.dtype != torch.float32 or not bias.is_contiguous())):
+            raise ValueError("act: h is [T, 3 H dh] of the type of q, bias [3 H dh] fp32")
+        hstu.mtgr_hstu_attn_bwd_act(p, jag.offsets, jag.seg, jag.ts, q, k, v, rab, dout, h, _token_stride(h, 3 * row),
+                                    bias, dq, dk, dv, drab, workspace, workspace.numel())
+        return dq, dk, dv, drab
     hstu.mtgr_hstu_attn_bwd(p, jag.offsets, jag.seg, jag.ts, q, k, v, rab, dout, dq, dk, dv, drab,
                             workspace, workspace.numel())
     return dq, dk, dv, drab
