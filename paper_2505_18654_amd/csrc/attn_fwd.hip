@@ -63,8 +63,9 @@ __device__ __forceinline__ uint4 ldg16(const uint16_t* p) { return *(const uint4
 // Splitting the keys (G = 2).  With few (user, head, query tile) items the chip idles and the longest
 // user sets the time.  A workgroup then has two groups of 4 waves, one workgroup per CU, that take
 // the item's visible key tiles in turn, each with its own LDS buffers, and the second group's O
-// is added to the first's through LDS at the end.  Both go through the same number of tiles (and
-// barriers): when it is odd, the second group ends with a tile whose keys are all hidden.
+// is added to the first's through LDS at the end.  Both pass the same number of barriers: when the
+// number of tiles is odd, the second group ends with a tile of which it takes the barrier only (its
+// products, with P = 0, would turn an infinite V into NaN).
 // Measured (serving users, 6 heads of 128): candidates of 8 users 65 -> 50 us, cached requests of
 // 1 / 4 / 8 users 21 -> 20, 33 -> 29 and 58 -> 49 us; one user of 3,000 tokens, 8 heads 40 -> 32 us.
 template <int DH, bool RAB, bool CACHED, bool RSEL, int G>
@@ -307,7 +308,8 @@ __global__ __launch_bounds__(256 * G, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     using F = std::false_type;
 
     // This group's next tile after tile t - 1, which the other group's next one precedes (group 1)
-    // or follows (group 0); *cls TILE_MASKED: the hidden last tile of group 1.
+    // or follows (group 0); *cls TILE_MASKED: the last tile of group 1 stands for a barrier only, and
+    // none follows it.
     auto next_of = [&](int t, int* cls) {
         if constexpr (G == 1) return walk.next(t, cls);
         int c;
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(256 * G, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
     };
     int cls0 = TILE_MASKED, cls1 = TILE_MASKED;
     int t0 = grp == 0 ? walk.next(0, &cls0) : next_of(0, &cls0);     // t_i
-    int t1 = t0 < ntk ? next_of(t0 + 1, &cls1) : ntk;            // t_{i+1}
+    int t1 = t0 < ntk && (G == 1 || cls0 != TILE_MASKED) ? next_of(t0 + 1, &cls1) : ntk;   // t_{i+1}
     // The workgroup's 128 query rows come in as two tiles, through the buffers of K(t_{i+1}) and
     // V(t_{i+1}) (copied later): whole rows per copy instruction, where per-lane loads of each
     // lane's operand chunks touched 32 rows per instruction (the forward took 12 % longer).
@@ -361,16 +363,17 @@ __global__ __launch_bounds__(256 * G, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
             if (tid < BN) {
                 // padded keys get code 0; every key gets its visibility threshold
                 int c = sVcode[P][tid];
-                if (t0 * BN + tid >= nkb || (G > 1 && cls0 == TILE_MASKED)) sVcode[P][tid] = c = 0;
+                if (t0 * BN + tid >= nkb) sVcode[P][tid] = c = 0;
                 const int kt = sVts[P][tid];
                 sVthr[P][tid] = key_threshold(c, kt);
                 if (RAB) sVts[P][tid] = (int)ts_key(kt);
             }
             lds_barrier();
+            if (G > 1 && cls0 == TILE_MASKED) return false;        // (its copies have landed: wait_vmem)
             if (t1 < ntk) issue_v(t1, P ^ 1);                      // V(t_{i-1})'s buffer
-            const bool partial = cls0 != TILE_FULL;
-            // (cached, hidden tile: no key is the query itself, so the diagonal test never holds)
-            const int qrel = CACHED || (G > 1 && cls0 == TILE_MASKED) ? -(1 << 20) : qi - t0 * BN - 4 * hh;
+            const bool partial = cls0 == TILE_PARTIAL;
+            // (cached: no key is the query itself, so the diagonal test never holds)
+            const int qrel = CACHED ? -(1 << 20) : qi - t0 * BN - 4 * hh;
             uint32_t pkA[4], pkB[4];
             // half 0 of t_i; next S = half 1 of t_i (same K buffer)
             if (SMASK && partial) premask(sA, C0{}, sVthr[P], qrel);
@@ -384,7 +387,7 @@ __global__ __launch_bounds__(256 * G, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
                 // middle: K(t_{i+1}) landed everywhere and K(t_i) is no longer read -> K(t_{i+2})
                 if (w == 0) wait_vmcnt<NK + 2>(); else wait_vmcnt<NK>();
                 lds_barrier();
-                t2 = next_of(t1 + 1, &cls2);
+                if (G == 1 || cls1 != TILE_MASKED) t2 = next_of(t1 + 1, &cls2);
                 if (t2 < ntk) issue_k(t2, P);
             }
             // half 1 of t_i; next S = half 0 of t_{i+1}.  After the last tile that S is formed

@@ -54,6 +54,38 @@ def test_split_forward(dh, rab):
     assert not off.any() and np.mean(a != b) < 0.02
 
 
+@pytest.mark.parametrize("dh,rab", [(32, 0), (64, 0), (128, 0), (128, 64)])
+@pytest.mark.parametrize("heads,lens,last", [(2, [(64, 0), (128, 0), (192, 0), (320, 0)], [40, 100, 150, 300]),
+                                             (1, [(192, 64 * 62)], [150])])
+def test_split_infinite_values(dh, rab, heads, lens, last):
+    """An infinity in V of the last visible tile (token `last` of each user): the same infinities and NaNs
+    as the unsplit forward, with 1, 2, 3 and 5 fully visible tiles, and with 62 fully masked ones, which
+    reach past the tile walker's first window of 64, behind three visible."""
+    segs = [[S] * n_s + [C] * n_c for n_s, n_c in lens]
+    rng = np.random.default_rng(dh)
+    tss = [sorted(rng.integers(-1000, 0, len(s)).tolist()) for s in segs]
+    few = custom_layout(segs, tss, heads=heads, head_dim=dh, rab_buckets=rab)
+    many = custom_layout(segs + [[S] * 30] * 250, tss + [[0] * 30] * 250, heads=heads, head_dim=dh, rab_buckets=rab)
+    T = few.total_tokens
+    at = torch.from_numpy(few.offsets[:-1].astype(np.int64) + np.array(last)).cuda()
+    outs = []
+    for L in (few, many):
+        inp = make_inputs(L, all_exact=True)
+        v = inp["v"].clone()
+        v[at, 0, 1], v[at, heads - 1, dh - 1] = float("inf"), float("-inf")
+        outs.append(ops.attn_fwd(inp["q"], inp["k"], v, jagged(inp), inp["rab"])[:T].float())
+    torch.cuda.synchronize()
+    split, whole = outs
+    inf, fin = torch.isinf(whole), torch.isfinite(whole)
+    say(f"[split] infinite V dh {dh} rab {rab}: {int(inf.sum())} infinities, {int(torch.isnan(whole).sum())} NaN")
+    assert int(inf.sum()) > T // 2
+    assert torch.equal(torch.isnan(split), torch.isnan(whole)) and torch.equal(torch.isinf(split), inf)
+    assert torch.equal(split[inf], whole[inf])
+    a, b = to_np(split[fin]), to_np(whole[fin])
+    off = np.abs(a - b) > 2.0 ** -7 * np.maximum(np.abs(a), np.abs(b)) + 1e-6 * np.sqrt(np.mean(b ** 2))
+    assert not off.any()
+
+
 @pytest.mark.parametrize("dh", [32, 64, 128])
 @pytest.mark.parametrize("cached", [[0, 1, 64, 65], [128, 150, 200, 256]])
 def test_split_cached(dh, cached):
