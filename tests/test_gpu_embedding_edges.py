@@ -64,13 +64,24 @@ def test_sgd_runs(counts, dim, dtype):
         assert ratio <= 1.0
 
 
-def test_insertion_from_freed_rows_and_the_tail_together():
-    """More new IDs than freed rows: the rest comes from the never-used rows, then nothing is left."""
-    t = DynamicEmbedding(1000, 8)
-    t.lookup(to_dev(np.arange(1, 501)), now=1, gather=False)
-    assert t.evict(2) == 500
-    _, b = t.lookup(to_dev(np.arange(1001, 2101)), now=3, gather=False)      # 1100 IDs for 1000 rows
+@pytest.mark.parametrize("cap,old,new", [(1000, 500, 1100), (2000, 1, 300), (60000, 30000, 65536), (150000, 70001, 200000)])
+def test_insertion_from_freed_rows_and_the_tail_together(cap, old, new):
+    """More new IDs than freed rows, in one and in many workgroups of both widths: the rest comes from the
+    never-used rows, then nothing is left.  Every row is handed out once."""
+    t = DynamicEmbedding(cap, 8)
+    t.lookup(to_dev(np.arange(1, old + 1)), now=1, gather=False)
+    assert t.evict(2) == old
+    _, b = t.lookup(to_dev(np.arange(old + 1, old + 1 + new)), now=3, gather=False)
+    got = min(cap, new)
     rows = b.rows.cpu().numpy()[:int(b.num_unique.item())]
     st = t.stats()
-    assert st["num_keys"] == 1000 and st["free_top"] == 0 and st["next_row"] == 1000 and st["overflow"] & 1
-    assert sorted(rows[rows >= 0].tolist()) == list(range(1000)) and (rows == -1).sum() == 100
+    assert st["num_keys"] == got and st["free_top"] == 0 and st["next_row"] == (cap if new > cap - old else max(old, got))
+    assert bool(st["overflow"] & 1) == (new > cap)
+    live = np.sort(rows[rows >= 0])
+    assert len(live) == got and (np.diff(live) > 0).all() and live[-1] < cap and (rows == -1).sum() == new - got
+    counts, seen = t.counts.cpu().numpy(), t.last_ts.cpu().numpy()
+    assert (counts[live] == 1).all() and (seen[live] == 3).all()
+    again = t.lookup(to_dev(np.arange(old + 1, old + 1 + new)), now=4, insert=False, gather=False)[1]
+    # (the unique list has an order of its own in each call: compared by ID)
+    by_id = lambda x: x.rows.cpu().numpy()[:new][np.argsort(x.unique.cpu().numpy()[:new])]
+    np.testing.assert_array_equal(by_id(again), by_id(b))
