@@ -256,7 +256,8 @@ __device__ __forceinline__ void zero_row(const EmbArgs& t, int row) {
 // (Finding and finishing used to be two launches and the clamping of the state a third: 24 us for
 // 319,887 IDs, 11 us for 8,000; now 27 and 5 us.  The unique list used to come in the order of the
 // set, in which the probes walk the key store; the scans that gave it that order cost 23 us.)
-__global__ void lookup_kernel(EmbArgs t, long long n_max, const uint64_t* __restrict__ unique,
+template <int TPB>
+__global__ __launch_bounds__(TPB) void lookup_kernel(EmbArgs t, long long n_max, const uint64_t* __restrict__ unique,
                               const int* __restrict__ occurrences, const long long* __restrict__ num_unique, int now,
                               int insert, int* __restrict__ rows) {
     const long long nu = min(*num_unique, n_max);
@@ -579,8 +580,15 @@ __global__ __launch_bounds__(THREADS) void sgd_sum_kernel(EmbArgs t, SgdWork w, 
     last_u[threadIdx.x] = cur;
 #pragma unroll
     for (int e = 0; e < epc; e++) last_part[threadIdx.x][e] = f[e];
+    // The IDs that reach beyond the workgroup, 0: over its start, 1: over its end only; their sums go out
+    // together at the end, whole lines per atomic instruction (one ID in all of 556,504 positions, dim 8:
+    // 8 atomics of one lane per workgroup made the step 104 us, 97.5 us before places were 1,024 per
+    // workgroup; now 75).
+    __shared__ float span_sum[2][1024];
+    __shared__ int span_id[2];
+    __shared__ long long span_group[2];
+    if (threadIdx.x < 2) span_id[threadIdx.x] = -1;
     __syncthreads();
-    if (runs == 0) return;
     // sum (from this chunk) of ID u whose part here is `part`; `reach`: it is the chunk's last run
     auto finish = [&](int u, const float* part, bool reach, int row, uint4 val) {
         float r[epc];
@@ -588,17 +596,36 @@ __global__ __launch_bounds__(THREADS) void sgd_sum_kernel(EmbArgs t, SgdWork w, 
         for (int e = 0; e < epc; e++) r[e] = part[e];
         bool to_end = false;      // reaches the workgroup's last place
         if (reach) {
+            // the chunks that hold nothing but u, then the first run of the next one; a hot ID fills
+            // up to 256 chunks, so their sums are read eight at a time (one after another: 1,000
+            // gradients of one ID, dim 8, 79 us; now 26)
+            const int chunks = min(cpb, (cnt + len - 1) / len);
             int cc = c + 1;
-            for (; cc < cpb && cc * len < cnt; cc++) {
-                const int pair = cc * cpr + j, fu = first_u[pair];
-                const bool whole = fu < 0 && last_u[pair] == u;      // the chunk holds nothing else
-                if (!whole && fu != u) break;
-                const float* q = whole ? last_part[pair] : first_part[pair];
+            for (bool open = true; open && cc < chunks;) {
+                float q[8][epc];
+                int fu[8], lu[8], whole = 0;
 #pragma unroll
-                for (int e = 0; e < epc; e++) r[e] += q[e];
-                if (!whole) break;
+                for (int k = 0; k < 8; k++) {
+                    const int pair = min(cc + k, chunks - 1) * cpr + j;
+                    fu[k] = first_u[pair];
+                    lu[k] = last_u[pair];
+#pragma unroll
+                    for (int e = 0; e < epc; e++) q[k][e] = last_part[pair][e];
+                }
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    open = open & (cc + k < chunks) & (fu[k] < 0) & (lu[k] == u);
+                    whole += open ? 1 : 0;
+#pragma unroll
+                    for (int e = 0; e < epc; e++) r[e] = open ? r[e] + q[k][e] : r[e];
+                }
+                cc += whole;
             }
-            to_end = cc >= cpb || cc * len >= cnt;
+            if (cc < chunks && first_u[cc * cpr + j] == u) {
+#pragma unroll
+                for (int e = 0; e < epc; e++) r[e] += first_part[cc * cpr + j][e];
+            }
+            to_end = cc >= chunks;
         }
         const bool from_start = c == 0 && lid[0] == u;
         long long group = blockIdx.x;
@@ -611,10 +638,13 @@ __global__ __launch_bounds__(THREADS) void sgd_sum_kernel(EmbArgs t, SgdWork w, 
         if (!spans) {
             if (row >= 0) apply_chunk<ESIZE>(vbase + row * vstride, val, r, lr);
         } else if (group >= 0 && group < w.groups) {
-            float* dst = w.acc + group * t.dim + j * epc;
+            const int which = from_start ? 0 : 1;
 #pragma unroll
-            for (int e = 0; e < epc; e++) atomicAdd(dst + e, r[e]);
-            if (group == blockIdx.x && j == 0) w.span[group] = u;
+            for (int e = 0; e < epc; e++) span_sum[which][j * epc + e] = r[e];
+            if (j == 0) {
+                span_id[which] = u;
+                span_group[which] = group;
+            }
         }
     };
     const int before = c > 0 ? last_u[threadIdx.x - cpr] : -1;
@@ -623,7 +653,15 @@ __global__ __launch_bounds__(THREADS) void sgd_sum_kernel(EmbArgs t, SgdWork w, 
         const uint4 val = row >= 0 ? *(const uint4*)(vbase + row * vstride) : make_uint4(0, 0, 0, 0);
         finish(first_id, first_part[threadIdx.x], false, row, val);
     }
-    if (runs > 1 || cur != before) finish(cur, last_part[threadIdx.x], true, crow, cval);
+    if (runs > 1 || (runs == 1 && cur != before)) finish(cur, last_part[threadIdx.x], true, crow, cval);
+    __syncthreads();
+#pragma unroll
+    for (int which = 0; which < 2; which++) {
+        if (span_id[which] < 0) continue;
+        const long long group = span_group[which];
+        for (int e = threadIdx.x; e < t.dim; e += THREADS) atomicAdd(w.acc + group * t.dim + e, span_sum[which][e]);
+        if (threadIdx.x == 0 && group == blockIdx.x) w.span[group] = span_id[which];
+    }
 }
 
 // The IDs that span workgroups: values[rows[u], :] -= lr * their accumulated sums.
