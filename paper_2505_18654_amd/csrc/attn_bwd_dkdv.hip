@@ -18,8 +18,12 @@ using bwd::zero;
 // complete in issue order), serialising copy and compute.
 // With STORE it also writes dS (bf16, the A operand of its dK product, masked but without the
 // factor 1 / n_b) as 64 x 64 blocks for the dQ-from-dS kernel; it forms drab when a.drab is set.
+// Waves per SIMD as many as a few registers fewer allow (left to itself the compiler takes 183 at dh 64
+// without a bias, 130 at dh 32 with one, and a wave per SIMD less runs: 128 users, 47 k tokens, 4
+// heads of 64, whole backward 144 us, with three 134).
 template <int DH, bool RAB, bool STORE, bool ACT>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2)) void attn_bwd_dkdv_bf16_kernel(
+    AttnArgs a) {
     constexpr int CPR = DH / 8, KSTEPS = DH / 16, DBLK = DH / 32, UNIT = 32 * DH;
     __shared__ __align__(16) uint16_t sK[BM * DH];
     // Query unit buffers: Q then dO of one unit in one array, so that a dO operand sits a constant

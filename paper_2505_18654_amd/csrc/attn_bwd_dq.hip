@@ -8,8 +8,10 @@ using bwd::ldg16;
 using bwd::zero;
 
 // ------------------------------------------------------------------ dQ (+ drab), bf16
+// (Three waves per SIMD at dh 64 with a bias: at the 170 registers that the compiler takes by itself two
+// run, and 128 users, 47 k tokens, 4 heads, 64 buckets take 150 us instead of 131.)
 template <int DH, bool RAB, bool ACT>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, DH == 64 && RAB ? 3 : 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     constexpr int CPR = DH / 8, KSTEPS = DH / 16, DBLK = DH / 32, TILE = BN * DH;
     __shared__ __align__(16) uint16_t sK0[TILE];
     __shared__ __align__(16) uint16_t sK1[TILE];
