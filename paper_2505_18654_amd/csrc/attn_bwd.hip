@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_vec_kernel(AttnArgs a) {
 
 // The relative bias enters the scores of both kernels (RAB_IN).  drab (a.drab) is formed by the
 // dK/dV kernel when it runs, else by the recomputing dQ kernel.
-template <int DH, bool RAB_IN, bool ACT>
+template <int DH, int RAB_IN, bool ACT>
 static hipError_t bwd_bf16_act(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
     if (plan.dkdv) {
         if (plan.store_ds) attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, true, ACT><<<slots, 256, 0, s>>>(a);
@@ -272,9 +272,16 @@ static hipError_t bwd_bf16_act(const AttnArgs& a, int slots, const BwdPlan& plan
     return hipSuccess;
 }
 
-template <int DH, bool RAB_IN>
-static hipError_t bwd_bf16_dh(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
+template <int DH, int RAB_IN>
+static hipError_t bwd_bf16_bias(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
     return a.act_h ? bwd_bf16_act<DH, RAB_IN, true>(a, slots, plan, s) : bwd_bf16_act<DH, RAB_IN, false>(a, slots, plan, s);
+}
+
+template <int DH>
+static hipError_t bwd_bf16_dh(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
+    if (!a.rab) return bwd_bf16_bias<DH, bwd::BIAS_NONE>(a, slots, plan, s);
+    return a.nbuckets == MTGR_RAB_LDS ? bwd_bf16_bias<DH, bwd::BIAS_FULL>(a, slots, plan, s)
+                                      : bwd_bf16_bias<DH, bwd::BIAS_FEWER>(a, slots, plan, s);
 }
 
 template <int DH, bool RAB_IN, class E>
@@ -293,11 +300,10 @@ static hipError_t bwd_vec_dh(const AttnArgs& a, int slots, bool dq, bool dkdv, h
 
 hipError_t launch_attn_bwd_bf16(const AttnArgs& a, int head_dim, int slots, const BwdPlan& plan,
                                 hipStream_t s) {
-    const bool rab = a.rab != nullptr;
     switch (head_dim) {
-        case 32: return rab ? bwd_bf16_dh<32, true>(a, slots, plan, s) : bwd_bf16_dh<32, false>(a, slots, plan, s);
-        case 64: return rab ? bwd_bf16_dh<64, true>(a, slots, plan, s) : bwd_bf16_dh<64, false>(a, slots, plan, s);
-        case 128: return rab ? bwd_bf16_dh<128, true>(a, slots, plan, s) : bwd_bf16_dh<128, false>(a, slots, plan, s);
+        case 32: return bwd_bf16_dh<32>(a, slots, plan, s);
+        case 64: return bwd_bf16_dh<64>(a, slots, plan, s);
+        case 128: return bwd_bf16_dh<128>(a, slots, plan, s);
         default: return hipErrorInvalidValue;
     }
 }

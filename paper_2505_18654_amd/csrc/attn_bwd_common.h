@@ -73,6 +73,17 @@ struct GradRows {
     }
 };
 
+// Relative bias of a backward kernel (RAB): none, one of all 64 buckets, or one of fewer.  With fewer the
+// numbers of rab_index end at the last bucket's, so that a run (HistRun) goes on over all gaps of it
+// (32 buckets: of more than 18 hours); the one operation for it costs 2 % with 64, where it does
+// nothing.  128 users, 47 k tokens, 4 heads, 32 buckets: dK/dV at dh 64 183 -> 167 us, at dh 128 224 ->
+// 212 us, dQ at dh 64 131 -> 116 us.
+enum { BIAS_NONE = 0, BIAS_FULL = 1, BIAS_FEWER = 2 };
+template <int RAB>
+__device__ __forceinline__ uint32_t bwd_index(uint32_t a, uint32_t b, int nb) {
+    return RAB == BIAS_FEWER ? min(rab_index(a, b), rab_last_index(nb)) : rab_index(a, b);
+}
+
 // drab histogram of one workgroup in LDS.  Log-time buckets put most (query, key) pairs of a
 // tile into a handful of buckets, so one histogram would serialise the 64 lanes of each LDS
 // atomic.  Lane l adds into copy l % 32 (at most two lanes of an instruction share a copy),
@@ -130,9 +141,9 @@ __device__ __forceinline__ void hist_finish(float* hist, int nb, float scale, fl
 }
 }  // namespace bwd
 
-template <int DH, bool RAB, bool ACT>
+template <int DH, int RAB, bool ACT>
 __global__ void attn_bwd_dq_bf16_kernel(AttnArgs a);
-template <int DH, bool RAB, bool STORE, bool ACT>
+template <int DH, int RAB, bool STORE, bool ACT>
 __global__ void attn_bwd_dkdv_bf16_kernel(AttnArgs a);
 template <int DH, bool ACT>
 __global__ void attn_bwd_dq_ds_bf16_kernel(AttnArgs a);

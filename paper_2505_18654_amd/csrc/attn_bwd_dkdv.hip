@@ -21,7 +21,7 @@ using bwd::zero;
 // Waves per SIMD as many as a few registers fewer allow (left to itself the compiler takes 183 at dh 64
 // without a bias, 130 at dh 32 with one, and a wave per SIMD less runs: 128 users, 47 k tokens, 4
 // heads of 64, whole backward 144 us, with three 134).
-template <int DH, bool RAB, bool STORE, bool ACT>
+template <int DH, int RAB, bool STORE, bool ACT>
 __global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2)) void attn_bwd_dkdv_bf16_kernel(
     AttnArgs a) {
     constexpr int CPR = DH / 8, KSTEPS = DH / 16, DBLK = DH / 32, UNIT = 32 * DH;
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2))
                 const int qb0 = 8 * (g0 >> 2) + 4 * hh;
                 const i32x4 qt4 = *(const i32x4*)&qts[qb0];
 #pragma unroll
-                for (int e = 0; e < 4; e++) bk[e] = rab_index((uint32_t)qt4[e], kkey);
+                for (int e = 0; e < 4; e++) bk[e] = bwd::bwd_index<RAB>((uint32_t)qt4[e], kkey, a.nbuckets);
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
                     // (the forward's scaled exponent, one operation fewer here, spilled two more
@@ -398,28 +398,40 @@ __global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2))
     }
 }
 
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, false, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, true, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, false, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, true, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, false, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, true, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, true, true>(AttnArgs);
 }  // namespace mtgr

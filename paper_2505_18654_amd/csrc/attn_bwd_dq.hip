@@ -10,7 +10,7 @@ using bwd::zero;
 // ------------------------------------------------------------------ dQ (+ drab), bf16
 // (Three waves per SIMD at dh 64 with a bias: at the 170 registers that the compiler takes by itself two
 // run, and 128 users, 47 k tokens, 4 heads, 64 buckets take 150 us instead of 131.)
-template <int DH, bool RAB, bool ACT>
+template <int DH, int RAB, bool ACT>
 __global__ __launch_bounds__(256, DH == 64 && RAB ? 3 : 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     constexpr int CPR = DH / 8, KSTEPS = DH / 16, DBLK = DH / 32, TILE = BN * DH;
     __shared__ __align__(16) uint16_t sK0[TILE];
@@ -121,7 +121,8 @@ __global__ __launch_bounds__(256, DH == 64 && RAB ? 3 : 2) void attn_bwd_dq_bf16
 #pragma unroll
                     for (int e = 0; e < GRP; e++) {
                         const int rr = g0 + e;
-                        bk[e] = rab_index(ts_key(qts), ts_key(kts[32 * blk + 8 * (rr >> 2) + 4 * hh + (rr & 3)]));
+                        bk[e] = bwd::bwd_index<RAB>(ts_key(qts), ts_key(kts[32 * blk + 8 * (rr >> 2) + 4 * hh + (rr & 3)]),
+                                                    a.nbuckets);
                     }
                 }
 #pragma unroll
@@ -201,16 +202,22 @@ __global__ __launch_bounds__(256, DH == 64 && RAB ? 3 : 2) void attn_bwd_dq_bf16
     rows.store(a, DQ, a.ld_q, sO, ob, nb, h, q0 + w * 32, lane);
 }
 
-template __global__ void attn_bwd_dq_bf16_kernel<32, false, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<32, false, true>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<32, true, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<32, true, true>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<64, false, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<64, false, true>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<64, true, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<64, true, true>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<128, false, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<128, false, true>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<128, true, false>(AttnArgs);
-template __global__ void attn_bwd_dq_bf16_kernel<128, true, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, bwd::BIAS_NONE, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, bwd::BIAS_NONE, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, bwd::BIAS_FULL, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, bwd::BIAS_FEWER, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, bwd::BIAS_FULL, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<32, bwd::BIAS_FEWER, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, bwd::BIAS_NONE, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, bwd::BIAS_NONE, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, bwd::BIAS_FULL, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, bwd::BIAS_FEWER, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, bwd::BIAS_FULL, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<64, bwd::BIAS_FEWER, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, bwd::BIAS_NONE, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, bwd::BIAS_NONE, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, bwd::BIAS_FULL, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, bwd::BIAS_FEWER, false>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, bwd::BIAS_FULL, true>(AttnArgs);
+template __global__ void attn_bwd_dq_bf16_kernel<128, bwd::BIAS_FEWER, true>(AttnArgs);
 }  // namespace mtgr

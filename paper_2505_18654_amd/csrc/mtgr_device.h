@@ -189,6 +189,8 @@ __device__ __forceinline__ uint32_t rab_index(uint32_t a, uint32_t b) {
     asm("v_sad_u32 %0, %1, %2, 0" : "=v"(g) : "v"(a), "v"(b));
     return __float_as_uint((float)(g & ~(g >> 2))) >> 22;
 }
+// Every larger index falls into the last bucket too.
+__device__ __forceinline__ uint32_t rab_last_index(int nb) { return 253u + (uint32_t)nb; }
 // slot 0: gap 0; 1: gap 1; 3 .. 64: buckets 2 .. 63
 __device__ __forceinline__ uint32_t rab_slot(uint32_t index) { return max(index, 253u) - 253u; }
 __device__ __forceinline__ int rab_slot_bucket(int slot, int nb) { return min(slot < 2 ? slot : slot - 1, nb - 1); }

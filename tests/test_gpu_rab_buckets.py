@@ -1,6 +1,6 @@
 """The relative bias at the edges of its buckets: time gaps one below, at and one above every
-2^e and 1.5 2^e up to 2^32 - 1 (from 2^24 on the gap does not fit a float), tables of 1, 2, 3, 9 and
-64 buckets, on the matrix-core kernels and both backward forms, against the oracle.  Bias values of
+2^e and 1.5 2^e up to 2^32 - 1 (from 2^24 on the gap does not fit a float), tables of 1, 2, 3, 9,
+32 and 64 buckets, on the matrix-core kernels and both backward forms, against the oracle.  Bias values of
 order 1 make a wrong bucket an error of order 1 in its rows.
 
 Bound: the operands P and dS and the results are each rounded to bf16 (relative error at most 2^-9
@@ -29,8 +29,8 @@ def gaps():
     return np.array(sorted(x for x in g if x < 2 ** 32), np.int64)
 
 
-@pytest.mark.parametrize("dh", [32, 128])
-@pytest.mark.parametrize("buckets", [1, 2, 3, 9, 64])
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("buckets", [1, 2, 3, 9, 32, 64])
 def test_bucket_edges(buckets, dh):
     ts = np.concatenate([[-2 ** 31], -2 ** 31 + gaps()]).astype(np.int32)
     segs = [np.ones(len(ts), np.int8), np.concatenate([np.ones(5, np.int8), np.full(len(ts) - 5, 2, np.int8)])]
