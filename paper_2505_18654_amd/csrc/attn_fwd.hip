@@ -518,7 +518,10 @@ __global__ __launch_bounds__(256 * G, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
 // the quad at a time: their partial scores are added across it with DPP, each thread takes the
 // SiLU and the mask of one of them, and the four P return to all.  (One key at a time, with shuffles
 // through LDS and every thread taking every SiLU, was one long dependence chain per key: forward of two
-// users of 200 tokens at dh 16 64 -> 28 us, of 64 users at dh 128 526 -> 303 us.)
+// users of 200 tokens at dh 16 64 -> 28 us, of 64 users at dh 128 526 -> 303 us.  At dh 64 and
+// 128 the keys past the user's end are not visited: four users of 24 tokens at dh 64 26 -> 11 us; with
+// fewer features the loop is unrolled over its constant length: one user of 2,000 tokens at dh 16
+// 106 us, 116 without.)
 template <int DH, bool RAB, class E>
 __global__ __launch_bounds__(256) void attn_fwd_vec_kernel(AttnArgs a) {
     constexpr int BMF = 64, SUB = DH <= 64 ? 64 : 32, Q4 = DH / 4;
@@ -563,8 +566,9 @@ __global__ __launch_bounds__(256) void attn_fwd_vec_kernel(AttnArgs a) {
         if (cls == TILE_MASKED) continue;
         for (int sub = 0; sub < BN / SUB; sub++) {
             const int kb = t * BN + sub * SUB;
+            const int keys = DH <= 32 ? SUB : min(SUB, (nb - kb + 3) & ~3);
             __syncthreads();
-            for (int i = tid; i < SUB * DH; i += 256) {
+            for (int i = tid; i < keys * DH; i += 256) {
                 const int row = i / DH, c = i % DH, key = kb + row;
                 sK[i] = key < nb ? ld_elem(K, (long long)(ob + key) * a.ld_k + h * DH + c) : 0.f;
                 sV[i] = key < nb ? ld_elem(V, (long long)(ob + key) * a.ld_v + h * DH + c) : 0.f;
@@ -576,7 +580,7 @@ __global__ __launch_bounds__(256) void attn_fwd_vec_kernel(AttnArgs a) {
             }
             __syncthreads();
 #pragma unroll (DH <= 32 ? 2 : 1)
-            for (int j = 0; j < SUB; j += 4) {
+            for (int j = 0; j < keys; j += 4) {
                 float s4[4];
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
