@@ -91,9 +91,10 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmArgs g) {
     const int wm = w & 1, wn = w >> 1;
     // Items (split, m block, n block), an equal share of consecutive ones per XCD (blockIdx % 8): the
     // n blocks of an m block, and the m blocks of a K split, run on one XCD, so that their rows
-    // stay in its L2.  (Dealing m blocks to XCDs left two of them without work at three m blocks;
-    // weight gradients at K = 70,176, d = 256: 54 -> 36 us, at K = 16,000, d = 128: 22 -> 17 us; at
-    // K = 6,925, d = 512 it is the slower one, 21 -> 25 us.)
+    // stay in its L2.  Dealing whole m blocks to XCDs left two of them without work at three m blocks, and
+    // gave some a round more than others (weight gradients at K = 70,176, d = 256: 54 -> 36 us; M = 5,000,
+    // N = 1536, K = 6144: 159 -> 97 us); where it did not, it was up to 12 % the faster (M = 8,300, N =
+    // K = 1024: 31 -> 35 us; M = 700, N = 640, K = 2560: 34 -> 38 us).
     const int tiles = g.mblocks * g.nblocks, items = tiles * g.splits, share = (items + XCDS - 1) / XCDS;
     const int item = blockIdx.x % XCDS * share + blockIdx.x / XCDS;
     if (item >= items) return;
@@ -490,26 +491,51 @@ __global__ __launch_bounds__(256) void gemm_split_reduce_kernel(GemmArgs g, int 
 }
 
 // Which kernel: 256 x 128 tiles, two workgroups per CU (gemm_bf16_kernel), or 256 x 256 tiles, one
-// per CU (gemm_wide_kernel).  The wide one does the same work 1.1 (K below 2048) to 1.25 times
-// faster, but in whole rounds of 256 tiles, and a lone tile takes twice as long.  So NN / NT take it
-// when rounds of the narrow one, twice as short, would not beat it: M = 70,176, N = 512, K = 2048
-// (3 rounds of wide, 5 half rounds of narrow) 171 -> 157 us; M = 33,000, N = 512 (2 and 3) 88 -> 94 us
-// stays; M = 6,925, N = 1024, K = 4096 (1 and 1) 66 -> 86 us stays.  With bias + SiLU, whose
-// element work dominates at small K, the wide one is the faster at every size up to K = 768
-// (M = 700, d = 128: 17.3 -> 13.9 us; d = 768: 25.3 -> 27.5 us).  TN takes it when its splits fill
-// about half the chip (M = N = 768, K = 6,925, 117 workgroups: 42 -> 32 us; 512, 52 workgroups: 21 ->
-// 31 us stays).
+// per CU (gemm_wide_kernel).  Both timed for the six products of a layer, d from 32 to 2,048 and 32 to
+// 100,000 rows; the lines below leave no size at which the wide one is chosen and is more than 3 %
+// (NN without an epilogue: 8 %, TN: 14 %) slower.
+//
+// NN / NT: the wide one does the same work up to 1.1 (K below 576), 1.15 (below 2048) or 1.25 times
+// faster, but in whole rounds of 256 tiles, and a lone tile takes 1.5 times as long.  So it is taken when
+// rounds of the narrow one, twice as short, would not beat it: M = 70,176, N = 512, K = 2048 (3
+// rounds of wide, 5 half rounds of narrow) 171 -> 157 us; M = 69,563, N = K = 1024 (5 and 9) 162 -> 156
+// us; M = 33,000, N = 512 (2 and 3) 88 us, wide 94; M = 6,925, N = 1024, K = 4096 (1 and 1) 66 us, wide 86.
+// Without an epilogue it pays for the k that pad the last step of 64 (N = K = 160, M = 60,000: 10.4 us,
+// wide 12.2), and NN, whose wide stores dominate, gains at most 1.07 (d = 256, [d, 4d], M = 90,000:
+// 61 us, wide 70).  With bias + SiLU, whose element work the wide one hides, it is 1.43 times faster up to
+// K = 768, and within a round also where it fills less of the chip than the narrow one, up to
+// K = 512 at any size (M = 700, d = 128: 17.3 -> 13.9 us), above from 128 narrow tiles on (d = 768: M = 700
+// 23.7 us, wide 24.8; M = 3,000 35.0 and 26.8).  At [d, 4d] with N no multiple of 256 the rounds count
+// the padding: d = 96, M = 36,000 20.8 us, wide 25.7.
+//
+// TN takes the wide one when its K splits fill about half the chip (M = N = 768, K = 6,925, 117
+// workgroups: 42 -> 32 us; 512, 52 workgroups: 21 us, wide 31), unless half of each tile would be
+// padding (M <= 128: d = 96, K = 70,000, [d, 4d] 32 us, wide 43), or one split's tiles leave much of
+// the chip idle for long (d = 1536, [d, 4d], 144 tiles, K = 45,000: 966 us, wide 1,241), or the narrow
+// one's few long splits fit the chip at once (64 tiles of 4 splits, K = 69,563, d = 1024, [d, 4d]: 534 us,
+// wide 580; d = 2048, d x d: 482, wide 510).
 static bool use_wide(const GemmArgs& g, long long mb, long long nb, long long nb_narrow) {
     auto rounds = [](long long tiles) { return (tiles + 255) / 256; };
-    if (mb * nb >= (1 << 20)) return false;
+    const long long wide = mb * nb, narrow = mb * nb_narrow;
+    if (wide == 0 || g.K == 0 || wide >= (1 << 20)) return false;     // (an empty product launches nothing)
     if (g.layout == GEMM_TN) {
-        const long long s = max(1ll, min(min(256 / max(mb * nb, 1ll), g.K / 512), 64ll));
-        return mb * nb * s >= 112;
+        const long long s = max(1ll, min(min(256 / max(wide, 1ll), g.K / 512), 64ll));
+        if (wide * s < 112 || g.M <= 128) return false;
+        if (s == 1) return wide >= 200 || g.K < 2048;
+        return s >= 8 || g.K < 24576 || narrow * ((512 + narrow - 1) / narrow) > 512;
     }
-    const bool silu = g.epilogue == GEMM_EPI_BIAS_SILU;
-    if (silu && g.K <= 768) return true;
-    const long long gain = silu || g.K >= 2048 ? 125 : 110;
-    return gain * rounds(mb * nb_narrow) >= 200 * rounds(mb * nb);
+    long long gain;
+    if (g.epilogue == GEMM_EPI_BIAS_SILU) {
+        if (wide <= 256 && (g.K <= 512 || (g.K <= 768 && narrow >= 128))) return true;
+        gain = g.K <= 768 ? 143 : 125;
+    } else {
+        gain = g.K >= 2048 ? 125 : g.K >= 576 ? 115 : 110;
+        if (g.epilogue == GEMM_EPI_NONE) {
+            if (g.layout == GEMM_NN && g.K < 2048) gain = g.K >= 768 ? 107 : g.K >= 448 ? 100 : 0;
+            gain = gain * g.K / (64 * ((g.K + 63) / 64));
+        }
+    }
+    return gain * rounds(narrow) >= 200 * rounds(wide);
 }
 
 void gemm_plan(GemmArgs* g) {

@@ -14,9 +14,10 @@ from tests.gpu_util import say
 pytestmark = pytest.mark.gpu
 
 
-# (bias + SiLU takes these tiles at every size with K <= 768)
+# (bias + SiLU takes these tiles at every size with K <= 512, and up to K = 768 from 128 of the narrow ones on)
 @pytest.mark.parametrize("M, N, K", [(1, 8, 32), (257, 264, 64), (256, 256, 96), (300, 520, 128), (255, 248, 160),
-                                     (513, 256, 192), (700, 1000, 736), (256 * 23 + 5, 256 * 12 + 8, 224)])
+                                     (513, 256, 192), (700, 1000, 512), (700, 1000, 736), (4100, 1000, 736),
+                                     (256 * 23 + 5, 256 * 12 + 8, 224)])
 def test_bias_silu(M, N, K):
     say(f"[gemm wide] bias+silu M={M} N={N} K={K}")
     A, B = rand_bf16((M, K), 5, cols=K + 8), rand_bf16((K, N), 6, scale=K ** -0.5 * 2)
@@ -37,7 +38,10 @@ def test_bias_silu(M, N, K):
     assert bool((full[M:] == 7.0).all()) and bool((full[:, N:] == 7.0).all())
 
 
-@pytest.mark.parametrize("M, N, K", [(256 * 32 - 3, 256 * 8 - 8, 96), (256 * 33 + 1, 256 * 16, 64)])
+# (the last three are on these tiles, one of them with two tiles per workgroup, the first two on the narrow ones)
+@pytest.mark.parametrize("M, N, K", [(256 * 32 - 3, 256 * 8 - 8, 96), (256 * 33 + 1, 256 * 16, 64),
+                                     (256 * 32 - 3, 256 * 8 - 8, 448), (256 * 32 - 3, 256 * 8 - 8, 800),
+                                     (256 * 64 - 3, 256 * 8, 448)])
 @pytest.mark.parametrize("layout", ["nn", "nt"])
 def test_plain(layout, M, N, K):
     say(f"[gemm wide] {layout} M={M} N={N} K={K}")
