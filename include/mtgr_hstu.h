@@ -260,7 +260,7 @@ mtgr_status_t mtgr_hstu_attn_bwd(const mtgr_hstu_problem_t* p, const int32_t* of
 /* mtgr_hstu_attn_bwd where q, k, v are activations silu(h + bias): writes the gradients of h, i.e.
  * dhq = dq silu'(h_q + bias_q) with dq rounded to the dtype first, and so on, bit for bit what
  * mtgr_bias_silu_bwd makes of dq, dk, dv.  h [T, 3 H dh] holds q's, k's and v's pre-activations side by
- * side (bf16, row stride ld_h, 16-byte rows), bias [3 H dh] fp32 or NULL.  bf16 with head_dim 32, 64
+ * side (bf16, row stride ld_h <= MTGR_MAX_LD, 16-byte rows), bias [3 H dh] fp32 or NULL.  bf16 with head_dim 32, 64
  * or 128. */
 mtgr_status_t mtgr_hstu_attn_bwd_act(const mtgr_hstu_problem_t* p, const int32_t* offsets,
                                      const int8_t* seg, const int32_t* ts, const void* q, const void* k,

@@ -492,6 +492,8 @@ mtgr_status_t mtgr_hstu_attn_bwd_act(const mtgr_hstu_problem_t* p, const int32_t
         REQUIRE_PTR(h, "h");
         if (ld_h < 3ll * p->num_heads * p->head_dim || ld_h % 8 != 0)
             return fail(MTGR_ERROR_INVALID_ARGUMENT, "ld_h = %lld (needs >= 3 H dh and a multiple of 8)", (long long)ld_h);
+        if (ld_h > MTGR_MAX_LD)
+            return fail(MTGR_ERROR_UNSUPPORTED, "ld_h %lld above %lld elements", (long long)ld_h, (long long)MTGR_MAX_LD);
         if (((uintptr_t)bias & 3u) != 0) return fail(MTGR_ERROR_INVALID_ARGUMENT, "bias is not 4-byte aligned");
     }
     return attn_bwd(p, offsets, seg, ts, q, k, v, rab, dout, h, ld_h, bias, dhq, dhk, dhv, drab, workspace,

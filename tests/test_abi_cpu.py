@@ -175,6 +175,21 @@ def test_bwd_argument_checks():
     assert len(args) == 12
 
 
+@pytest.mark.parametrize("ld_h,kw,status", [
+    (376, {}, hstu.MTGR_ERROR_INVALID_ARGUMENT),                     # below 3 H dh = 384
+    (388, {}, hstu.MTGR_ERROR_INVALID_ARGUMENT),                     # rows not of 16 bytes
+    (hstu.MTGR_MAX_LD + 8, {}, hstu.MTGR_ERROR_UNSUPPORTED),
+    (384, dict(head_dim=16), hstu.MTGR_ERROR_UNSUPPORTED),           # the vector kernels
+    (384, dict(dtype=FP32), hstu.MTGR_ERROR_UNSUPPORTED),
+])
+def test_bwd_act_argument_checks(ld_h, kw, status):
+    p = prob(**{**dict(heads=2, head_dim=64), **kw})
+    with pytest.raises(hstu.MtgrError) as e:
+        hstu.mtgr_hstu_attn_bwd_act(p, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, None, FAKE, FAKE, ld_h, FAKE, FAKE, FAKE,
+                                    FAKE, None, FAKE, 1 << 30, 0)
+    assert e.value.status == status
+
+
 def test_backward_workspace_sizes():
     """backward = 1 adds the stored-dS blocks for bf16: H * ntile * (T/64 + B) blocks of 8 KB
     on top of the plan; fp32 always recomputes, so its size does not grow."""
