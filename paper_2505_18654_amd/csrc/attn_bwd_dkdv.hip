@@ -1,4 +1,6 @@
 // dK, dV (and drab, and optionally the stored dS blocks) of the attention backward (bf16).
+#include <type_traits>
+
 #include "attn_bwd_common.h"
 
 namespace mtgr {
@@ -355,8 +357,8 @@ __global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2))
     }
     // dK^T / dV^T accumulators: lane = key row, registers = features, so that a lane packs four
     // consecutive features per LDS write (as dK / dV, lane = feature, each value was a 2-byte
-    // write of its own: 1,208 -> 1,197 us on 64 users with 66 k tokens, 8 heads of 128).  Each wave stages its 32 rows in a swizzled 32-row tile inside
-    // the K tile.
+    // write of its own: 1,208 -> 1,197 us on 64 users with 66 k tokens, 8 heads of 128).  Each wave
+    // stages its 32 rows in a swizzled 32-row tile inside the K tile.
     uint16_t* sO = sK + w * 32 * DH;
     const float dk_scale = alpha * inv_n, dv_scale = RAB ? inv_n : alpha * inv_n;
     uint16_t* DK = (uint16_t*)a.dk;
@@ -389,6 +391,7 @@ __global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2))
         if constexpr (PRELOAD || !ACT) {
             rows[which].store(a, dst, ld, sO, ob, nb, h, k0 + w * 32, lane);
         } else {
+            // (the kernel's only argument, so its kernarg segment begins with it: asserted below)
             const AttnArgs* args = (const AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
             asm volatile("" : "+s"(args));
             bwd::GradRows<DH, ACT> late;
@@ -397,6 +400,9 @@ __global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2))
         }
     }
 }
+
+static_assert(std::is_same_v<decltype(&attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, true>), void (*)(AttnArgs)>,
+              "the arguments are read again from the start of the kernarg segment");
 
 template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, false>(AttnArgs);
 template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, true>(AttnArgs);
