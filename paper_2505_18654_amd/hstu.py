@@ -171,6 +171,15 @@ def _ptr(x) -> Optional[int]:
 _raw_stream = None
 
 
+def _forget_stream() -> None:
+    global _raw_stream
+    _raw_stream = None
+
+
+# A forked child cannot use its parent's CUDA state, and torch.cuda.current_stream() says so.
+os.register_at_fork(after_in_child=_forget_stream)
+
+
 def _current_stream() -> int:
     """The handle of torch's current stream on the current device.  Asked for once per call, so it
     goes past the Stream object that torch.cuda.current_stream() builds (2.7 of a call's 12 us)."""

@@ -190,6 +190,16 @@ def test_bwd_act_argument_checks(ld_h, kw, status):
     assert e.value.status == status
 
 
+def test_stream_handle_is_asked_for_again_after_a_fork(monkeypatch):
+    """A forked child cannot use the parent's device: torch says so when its stream is asked for, which the
+    parent's kept handle lookup must not bypass."""
+    monkeypatch.setattr(hstu, "_raw_stream", lambda: 0)
+    pid = os.fork()
+    if pid == 0:
+        os._exit(0 if hstu._raw_stream is None else 1)
+    assert os.waitpid(pid, 0)[1] == 0 and hstu._raw_stream is not None
+
+
 def test_backward_workspace_sizes():
     """backward = 1 adds the stored-dS blocks for bf16: H * ntile * (T/64 + B) blocks of 8 KB
     on top of the plan; fp32 always recomputes, so its size does not grow."""
