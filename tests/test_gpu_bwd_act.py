@@ -41,13 +41,16 @@ def test_bits(dh, stored, rab_on, bias_on):
         g = tuple(da[:, i * d:(i + 1) * d].view(T, H, dh) for i in range(3)) + (
             None if rab is None else torch.empty_like(rab),)
         ops.attn_bwd(q, k, v, do, jag, rab, grads=g, workspace=ws, act=act)
-        return da
+        return da, g[3]
 
-    want = grads(None)
+    want, want_drab = grads(None)
     hstu.mtgr_bias_silu_bwd(T, 4 * d, hstu.MTGR_DTYPE_BF16, h, 4 * d, bias, want, 4 * d, want, 4 * d)
-    got = grads((h[:, :3 * d], None if bias is None else bias[:3 * d]))
+    got, drab = grads((h[:, :3 * d], None if bias is None else bias[:3 * d]))
     torch.cuda.synchronize()
     assert torch.equal(got[:, :3 * d], want[:, :3 * d]) and not got[:, 3 * d:].any()
+    # (drab is of the bias in both; float atomics: 1e-5 of its size, as in test_gpu_rab_buckets.py)
+    if rab is not None:
+        assert float((drab - want_drab).abs().max()) <= 1e-5 * float(want_drab.abs().max()) and want_drab.any()
 
 
 @pytest.mark.parametrize("heads,dh", [(2, 16), (2, 32), (1, 128)])
