@@ -85,6 +85,14 @@ enum {
 
 typedef void* mtgr_stream_t;            /* hipStream_t */
 
+/* Results of the attention and of the dense products are deterministic for given sizes, but for drab
+ * (float atomics).  They are not independent of the sizes: a small problem's forward (bf16, head_dim
+ * 32 to 128) takes the keys of a row in two interleaved parts, a large one's in one, which
+ * total_tokens, num_users, num_heads and max_seqlen (a bound: a looser one counts too) decide, and M, N and K
+ * decide the tiles of a product.  So the fp32 sums of one user's rows can be in another order
+ * in another batch, or when max_seqlen is given differently, and differ in the last bit of the
+ * result; every row of one call is formed the same way. */
+
 /* Shape of one attention call.
  *   num_users B >= 0, total_tokens T >= 0 (T < 2^31), max_seqlen >= every user's length.
  *   num_heads H in 1..255; head_dim dh in {16, 32, 64, 128} for both dtypes.  bf16 at
@@ -188,7 +196,7 @@ mtgr_status_t mtgr_hstu_attn_fwd(const mtgr_hstu_problem_t* p, const int32_t* of
  * (every token of the user, as in mtgr_hstu_attn_fwd), M_ij the mask of Sec. 4.2 from the
  * cached tokens' segments (in the cache plan) and timestamps.  This equals the candidate rows
  * of mtgr_hstu_attn_fwd on the concatenated sequence [cached | candidates] up to the order of
- * the float sums.  (The user side of the first layer depends only on the user; at deeper layers
+ * the float sums (also where all tiles are the same: the two calls are of different sizes, see the top).  (The user side of the first layer depends only on the user; at deeper layers
  * it also depends on n_b, so a cache serves requests with the same candidate count.)
  *   p: the request: B users, T = all candidates, max_seqlen >= candidates of any user; its
  *     tokens should be candidates (seg = MTGR_SEG_CAND); q, k, v, out [T, H, dh] bf16.

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_vec_kernel(AttnArgs a) {
     }
 }
 
-// dkdv kernel: 64 key rows, 4 threads per key; queries staged 32 at a time.
+// dkdv kernel: 64 key rows, 4 threads per key; queries staged 64 (32 at dh 128) at a time.
 template <int DH, bool RAB, class E>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_vec_kernel(AttnArgs a) {
     constexpr int BMF = 64, SUB = DH <= 64 ? 64 : 32, Q4 = DH / 4;

@@ -626,7 +626,8 @@ static hipError_t fwd_bf16_groups(const AttnArgs& a, int slots, hipStream_t s) {
 // Two groups per workgroup pay while every item has a CU to itself, so up to about 256 items; the
 // host knows the work list's slots, an upper bound.  Forwards of 72 to 328 slots took 0.77 to 0.97
 // of their time with one group, 376 slots (32 users of 180 tokens) 1.09, 536 to 872 (24 to 32
-// serving users) 1.2 to 1.36.
+// serving users) 1.2 to 1.36.  The slots follow from total_tokens, num_users, num_heads and the caller's
+// max_seqlen, so these decide the order of a row's fp32 sums (stated in mtgr_hstu.h).
 constexpr int SPLIT_SLOTS = 320;
 
 template <int DH, bool CACHED>

@@ -255,7 +255,10 @@ __device__ __forceinline__ void zero_row(const EmbArgs& t, int row) {
 // make fewer grants.
 // (Finding and finishing used to be two launches and the clamping of the state a third: 24 us for
 // 319,887 IDs, 11 us for 8,000; now 27 and 5 us.  The unique list used to come in the order of the
-// set, in which the probes walk the key store; the scans that gave it that order cost 23 us.)
+// set, in which the probes walk the key store; the scans that gave it that order cost 23 us.  Beyond
+// about two million distinct IDs in one call the order was worth more than the scans: de-duplication and
+// lookup of 1.5 million known ones 270 -> 262 us, of 4 million 650 -> 710, of 16 million 2,770 -> 3,410 us;
+// of 4 and 16 million Zipf IDs 490 -> 485 and 1,970 -> 2,100 us.)
 template <int TPB>
 __global__ __launch_bounds__(TPB) void lookup_kernel(EmbArgs t, long long n_max, const uint64_t* __restrict__ unique,
                               const int* __restrict__ occurrences, const long long* __restrict__ num_unique, int now,

@@ -109,7 +109,10 @@ def workspace_for(problem: hstu.HstuProblem, device, backward: bool = False) -> 
 def attn_fwd(q, k, v, jag: Jagged, rab=None, alpha: float = 1.0, out=None, workspace=None,
              planned: bool = False, cand_rows: bool = False):
     """Eq. 5 forward: returns out [T, H, dh] (same dtype as q).  cand_rows=True forms only the
-    candidate tokens' rows (the other rows of `out` are left as they were)."""
+    candidate tokens' rows (the other rows of `out` are left as they were).
+
+    A row's fp32 sums are in an order that the batch's sizes decide (total tokens, users, heads, and
+    jag.max_seqlen), so the same user can differ in a result's last bit between batches."""
     if out is None:
         out = torch.empty_like(q, memory_format=torch.contiguous_format)
     flags = (hstu.MTGR_ATTN_PLANNED if planned else 0) | (hstu.MTGR_FWD_CAND_ROWS if cand_rows else 0)
