@@ -777,7 +777,7 @@ hipError_t launch_emb_lookup(const EmbArgs& t, long long n_max, const uint64_t* 
     if (n_max <= BATCH_SMALL)
         lookup_kernel<THREADS><<<grid_for(n_max), THREADS, 0, s>>>(t, n_max, unique, occ, num_unique, now, insert, rows);
     else
-        lookup_kernel<1024><<<(int)min((n_max + 1023) / 1024, 2048ll), 1024, 0, s>>>(t, n_max, unique, occ, num_unique,
+        lookup_kernel<512><<<(int)min((n_max + 511) / 512, 4096ll), 512, 0, s>>>(t, n_max, unique, occ, num_unique,
                                                                                    now, insert, rows);
     return hipGetLastError();
 }

@@ -493,7 +493,7 @@ __global__ __launch_bounds__(256) void gemm_split_reduce_kernel(GemmArgs g, int 
 // Which kernel: 256 x 128 tiles, two workgroups per CU (gemm_bf16_kernel), or 256 x 256 tiles, one
 // per CU (gemm_wide_kernel).  Both timed for the six products of a layer, d from 32 to 2,048 and 32 to
 // 100,000 rows; the lines below leave no size at which the wide one is chosen and is more than 3 %
-// (NN without an epilogue: 8 %, TN: 14 %) slower.
+// (NN without an epilogue: 8 %, TN: 14 %) slower in a program of its own.
 //
 // NN / NT: the wide one does the same work up to 1.1 (K below 576), 1.15 (below 2048) or 1.25 times
 // faster, but in whole rounds of 256 tiles, and a lone tile takes 1.5 times as long.  So it is taken when
@@ -511,18 +511,17 @@ __global__ __launch_bounds__(256) void gemm_split_reduce_kernel(GemmArgs g, int 
 // TN takes the wide one when its K splits fill about half the chip (M = N = 768, K = 6,925, 117
 // workgroups: 42 -> 32 us; 512, 52 workgroups: 21 us, wide 31), unless half of each tile would be
 // padding (M <= 128: d = 96, K = 70,000, [d, 4d] 32 us, wide 43), or one split's tiles leave much of
-// the chip idle for long (d = 1536, [d, 4d], 144 tiles, K = 45,000: 966 us, wide 1,241), or the narrow
-// one's few long splits fit the chip at once (64 tiles of 4 splits, K = 69,563, d = 1024, [d, 4d]: 534 us,
-// wide 580; d = 2048, d x d: 482, wide 510).
+// the chip idle for long (d = 1536, [d, 4d], 144 tiles, K = 45,000: 966 us, wide 1,241).  Where both fill the
+// chip once (d = 1024, [d, 4d], K = 79,372, 4 splits) it depends on the power that the data takes: on
+// activations narrow 618 us, wide 661, on the gradients of a layer 595 and 576, and there the narrow
+// one also slows the kernels around it by 1 to 2 %; the wide one stays.
 static bool use_wide(const GemmArgs& g, long long mb, long long nb, long long nb_narrow) {
     auto rounds = [](long long tiles) { return (tiles + 255) / 256; };
     const long long wide = mb * nb, narrow = mb * nb_narrow;
     if (wide == 0 || g.K == 0 || wide >= (1 << 20)) return false;     // (an empty product launches nothing)
     if (g.layout == GEMM_TN) {
         const long long s = max(1ll, min(min(256 / max(wide, 1ll), g.K / 512), 64ll));
-        if (wide * s < 112 || g.M <= 128) return false;
-        if (s == 1) return wide >= 200 || g.K < 2048;
-        return s >= 8 || g.K < 24576 || narrow * ((512 + narrow - 1) / narrow) > 512;
+        return wide * s >= 112 && g.M > 128 && (s > 1 || wide >= 200 || g.K < 2048);
     }
     long long gain;
     if (g.epilogue == GEMM_EPI_BIAS_SILU) {
