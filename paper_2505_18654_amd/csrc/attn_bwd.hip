@@ -254,8 +254,12 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_vec_kernel(AttnArgs a) {
 template <int DH, int RAB_IN, bool ACT>
 static hipError_t bwd_bf16_act(const AttnArgs& a, int slots, const BwdPlan& plan, hipStream_t s) {
     if (plan.dkdv) {
-        if (plan.store_ds) attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, true, ACT><<<slots, 256, 0, s>>>(a);
-        else attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, false, ACT><<<slots, 256, 0, s>>>(a);
+        // (the only instantiation whose registers cost it a wave; 512: two workgroups per CU)
+        constexpr bool HAS_FEW = DH == 64 && RAB_IN == bwd::BIAS_NONE && !ACT;
+        if (plan.store_ds && HAS_FEW && slots <= 512)
+            attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, true, ACT, HAS_FEW><<<slots, 256, 0, s>>>(a);
+        else if (plan.store_ds) attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, true, ACT, false><<<slots, 256, 0, s>>>(a);
+        else attn_bwd_dkdv_bf16_kernel<DH, RAB_IN, false, ACT, false><<<slots, 256, 0, s>>>(a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

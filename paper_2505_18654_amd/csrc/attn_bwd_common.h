@@ -143,7 +143,7 @@ __device__ __forceinline__ void hist_finish(float* hist, int nb, float scale, fl
 
 template <int DH, int RAB, bool ACT>
 __global__ void attn_bwd_dq_bf16_kernel(AttnArgs a);
-template <int DH, int RAB, bool STORE, bool ACT>
+template <int DH, int RAB, bool STORE, bool ACT, bool FEW>
 __global__ void attn_bwd_dkdv_bf16_kernel(AttnArgs a);
 template <int DH, bool ACT>
 __global__ void attn_bwd_dq_ds_bf16_kernel(AttnArgs a);

@@ -20,12 +20,14 @@ using bwd::zero;
 // complete in issue order), serialising copy and compute.
 // With STORE it also writes dS (bf16, the A operand of its dK product, masked but without the
 // factor 1 / n_b) as 64 x 64 blocks for the dQ-from-dS kernel; it forms drab when a.drab is set.
-// Waves per SIMD as many as a few registers fewer allow (left to itself the compiler takes 183 at dh 64
-// without a bias, 130 at dh 32 with one, and a wave per SIMD less runs: 128 users, 47 k tokens, 4
-// heads of 64, whole backward 144 us, with three 134).
-template <int DH, int RAB, bool STORE, bool ACT>
-__global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2)) void attn_bwd_dkdv_bf16_kernel(
-    AttnArgs a) {
+// Waves per SIMD as many as a few registers fewer allow, for the two instantiations that the compiler by
+// itself gives a few too many (storing dS: 183 at dh 64 without a bias and activation, 130 at dh 32 with a
+// bias), so that a wave per SIMD less would run: 128 users, 47 k tokens, 4 heads of 64, whole
+// backward 144 us, with three waves 134.  (The others are up to 5 % slower with the same bound.)  FEW, for work lists that leave at most two
+// workgroups to a CU, keeps the registers instead (a training step of 32 short users 75.6 -> 74.2 us).
+template <int DH, int RAB, bool STORE, bool ACT, bool FEW>
+__global__ __launch_bounds__(
+    256, !STORE ? 2 : RAB ? (DH == 32 ? 4 : 2) : (DH == 64 && !ACT && !FEW ? 3 : 2)) void attn_bwd_dkdv_bf16_kernel(AttnArgs a) {
     constexpr int CPR = DH / 8, KSTEPS = DH / 16, DBLK = DH / 32, UNIT = 32 * DH;
     __shared__ __align__(16) uint16_t sK[BM * DH];
     // Query unit buffers: Q then dO of one unit in one array, so that a dO operand sits a constant
@@ -401,43 +403,44 @@ __global__ __launch_bounds__(256, RAB ? (DH == 32 ? 4 : 2) : (DH == 64 ? 3 : 2))
     }
 }
 
-static_assert(std::is_same_v<decltype(&attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, true>), void (*)(AttnArgs)>,
+static_assert(std::is_same_v<decltype(&attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, true, false>), void (*)(AttnArgs)>,
               "the arguments are read again from the start of the kernarg segment");
 
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, false, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, false, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, true, false>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, true, true>(AttnArgs);
-template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, true, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_NONE, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FULL, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<32, bwd::BIAS_FEWER, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, true, false, true>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_NONE, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FULL, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<64, bwd::BIAS_FEWER, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_NONE, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, false, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, false, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, true, false, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FULL, true, true, false>(AttnArgs);
+template __global__ void attn_bwd_dkdv_bf16_kernel<128, bwd::BIAS_FEWER, true, true, false>(AttnArgs);
 }  // namespace mtgr
